@@ -412,9 +412,17 @@ typedef struct wpm_batch {
     int32_t max_kp;            /* max over the tables swept of max(k, 7), <= WPM_MAX_K */
     const uint32_t *d_tables;  /* device: packed tables, concatenated (16-byte aligned each) */
     const int64_t *d_offsets;  /* device: word offset of each table in d_tables */
-    int32_t flags;             /* reserved, 0 */
+    int32_t flags;             /* WPM_BATCH_*, or 0: nothing said about the tables */
     int32_t reserved;
 } wpm_batch;
+
+/* Two kernels share the sweep: tables with a level section (header word 11,
+ * bit 1, set by wpm_pack_instance when the sub-cube tests reject enough) are
+ * descended as a tree, the others walked vector by vector.  A batch that says
+ * that all of its tables are of one kind is spared the other's launch; an
+ * item whose table is of the other kind is then malformed (d_total[2]). */
+#define WPM_BATCH_TREE 1 /* every table swept has a level section */
+#define WPM_BATCH_WALK 2 /* none has */
 
 #define WPM_FLAG_ACCUMULATE 1 /* do not clear d_counts, d_total, d_stats: add to them */
 
@@ -466,11 +474,14 @@ int wpm_persistent_grid(const wpm_batch *batch, int32_t wg_size, int32_t *grid);
  *               wpm_collect returns WPM_ECAP; counts stay exact), [2] malformed
  *               items skipped (wpm_collect then returns WPM_EINVAL), [3] 0
  *   d_stats     optional [8] uint64 device counters: [0] candidates (vectors
- *               passing the fast filter), [1] vectors passing every resident
- *               ridge group, [2] of those, vectors rejected by the facet bound,
- *               the properties or a deferred ridge, [3] wave passes over the
- *               listed candidates, [4] wave steps whose candidates overflowed
- *               the list and were rechecked
+ *               passing the fast tests: the fast filter of a walked table,
+ *               the sub-cube and leaf tests of a descended one), [1] vectors
+ *               passing every resident ridge group, [2] of those, vectors
+ *               rejected by the facet bound, the properties or a deferred
+ *               ridge, [3] wave passes over the listed candidates, [4] wave
+ *               steps whose candidates overflowed the list, [5..7] sub-cubes of
+ *               2^18, 2^12 and 2^6 vectors that the descent opened (waves that
+ *               share one count it each)
  * Items must lie inside their instance's 2^max(k,7) Gray range with
  * 7 <= cbits <= max(k, 7), 1 <= lanes <= wg_size, and first mod
  * WPM_LANE_WINDOW + lanes <= WPM_LANE_WINDOW (wpm_build_queue and

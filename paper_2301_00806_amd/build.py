@@ -25,8 +25,8 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function"]
 DEVICE = [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 SOURCES = ["prep.cpp", "prune.cpp", "conditions.cpp", "orbits.cpp", "complexes.cpp", "sched.cpp", "capi.cpp", "engine.hip", "mlp.hip", "probe.hip",
-           "sweep.hip"]
-EXTRA = {"sweep.hip": ["-mllvm", "-disable-machine-licm"]}
+           "sweep.hip", "tree.hip"]
+EXTRA = {src: ["-mllvm", "-disable-machine-licm"] for src in ("sweep.hip", "tree.hip")}
 
 
 def _compile(src: str) -> str:

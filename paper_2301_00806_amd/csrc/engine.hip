@@ -12,15 +12,22 @@
 
 #include "internal.h"
 #include "launch.h"
+#include "tree_kernel.h"
 
 namespace wpm {
 
 namespace {
 thread_local char g_hip_err[256] = "no HIP error";
 
-__global__ void zero_u64(unsigned long long *p, int64_t n) {
+// The words a sweep accumulates into, cleared in one launch: four separate
+// fills were most of a small sweep's launches.
+__global__ void clear_outputs(unsigned long long *counts, int64_t num, unsigned long long *total,
+                              unsigned long long *stats, unsigned long long *head) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0ull;
+    if (counts && i < num) counts[i] = 0ull;
+    if (total && i < WPM_TOTAL_WORDS) total[i] = 0ull;
+    if (stats && i < 8) stats[i] = 0ull;
+    if (head && i < 2) head[i] = 0ull;
 }
 
 int hip_fail(const char *what, hipError_t e) {
@@ -34,14 +41,10 @@ int hip_fail(const char *what, hipError_t e) {
         if (_e != hipSuccess) return hip_fail(#expr, _e); \
     } while (0)
 
-int zero(void *p, int64_t n, hipStream_t st) {
-    if (!p || n <= 0) return WPM_OK;
-    const int bs = 256;
-    const int64_t nb = (n + bs - 1) / bs;
-    hipLaunchKernelGGL(zero_u64, dim3((unsigned)nb), dim3(bs), 0, st, (unsigned long long *)p, n);
-    HIP_TRY(hipGetLastError());
-    return WPM_OK;
-}
+// Which kernels a batch needs: the descent for tables with a level section,
+// the walk for the others (a batch that does not say gets both).
+bool wants_tree(const wpm_batch *b) { return !(b->flags & WPM_BATCH_WALK); }
+bool wants_walk(const wpm_batch *b) { return !(b->flags & WPM_BATCH_TREE); }
 
 // Waves per SIMD of the kernel a schedule asks for (0: the default, 8).
 int pick_waves(int w) { return w == 7 ? 7 : 8; }
@@ -82,12 +85,15 @@ int persistent_grid_waves(const wpm_batch *b, int wg_size, int waves, int32_t *g
     if (!b || !grid || wg_size < 64 || wg_size > 512 || (wg_size % 64)) return WPM_EINVAL;
     if (b->max_row_words < 4 || b->max_row_words > WPM_MAX_ROW_WORDS || (b->max_row_words & 3)) return WPM_EINVAL;
     if (b->max_kp < 7 || b->max_kp > WPM_MAX_K) return WPM_EINVAL;
-    const size_t lds = sweep_lds_bytes(b->max_kp, b->max_row_words, wg_size);
     int32_t cus = 0;
     int rc = device_query(&cus, nullptr, nullptr);
     if (rc) return rc;
     int nb = 0;
-    HIP_TRY(occupancy_sweep(pick_waves(waves), &nb, wg_size, lds));
+    if (wants_tree(b))
+        HIP_TRY(occupancy_tree(&nb, wg_size, tree_lds_bytes(b->max_kp, b->max_row_words, wg_size)));
+    else
+        HIP_TRY(occupancy_sweep(pick_waves(waves), &nb, wg_size,
+                                sweep_lds_bytes(b->max_kp, b->max_row_words, wg_size)));
     *grid = std::max(1, nb) * cus;
     return WPM_OK;
 }
@@ -111,20 +117,25 @@ int enumerate_with(const wpm_batch *b, const wpm_sched *s, uint64_t *d_surv, uin
     if (s->waves_per_simd != 0 && s->waves_per_simd != 7 && s->waves_per_simd != 8) return WPM_EINVAL;
     hipStream_t st = (hipStream_t)stream;
     const int waves = pick_waves(s->waves_per_simd);
-    const size_t lds = sweep_lds_bytes(b->max_kp, b->max_row_words, s->wg_size);
+    if ((b->flags & WPM_BATCH_TREE) && (b->flags & WPM_BATCH_WALK)) return WPM_EINVAL;
+    const bool tree = wants_tree(b), walk = wants_walk(b);
+    const size_t lds = walk ? sweep_lds_bytes(b->max_kp, b->max_row_words, s->wg_size) : 0;
+    const size_t tree_lds = tree ? tree_lds_bytes(b->max_kp, b->max_row_words, s->wg_size) : 0;
     int32_t lds_max = 0;
     if (cap >= (UINT64_MAX >> 2)) return WPM_EINVAL;
     int rc = device_query(nullptr, nullptr, &lds_max);
     if (rc) return rc;
-    if (lds > (size_t)lds_max) return WPM_ELIMIT;
+    if (std::max(lds, tree_lds) > (size_t)lds_max) return WPM_ELIMIT;
 
-    int st_rc;
-    if (!(s->flags & WPM_FLAG_ACCUMULATE)) {
-        if ((st_rc = zero(d_counts, b->num_instances, st))) return st_rc;
-        if ((st_rc = zero(d_total, WPM_TOTAL_WORDS, st))) return st_rc;
-        if ((st_rc = zero(d_stats, 8, st))) return st_rc;
+    const bool clear = !(s->flags & WPM_FLAG_ACCUMULATE);
+    if (clear || d_head) {
+        const int64_t n = clear ? std::max<int64_t>(b->num_instances, 8) : 8;
+        hipLaunchKernelGGL(clear_outputs, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
+                           (unsigned long long *)(clear ? d_counts : nullptr), (int64_t)b->num_instances,
+                           (unsigned long long *)(clear ? d_total : nullptr),
+                           (unsigned long long *)(clear ? d_stats : nullptr), (unsigned long long *)d_head);
+        HIP_TRY(hipGetLastError());
     }
-    if (d_head && (st_rc = zero(d_head, 2, st))) return st_rc;
     if (s->num_items == 0) return WPM_OK;
 
     KArgs a;
@@ -141,10 +152,53 @@ int enumerate_with(const wpm_batch *b, const wpm_sched *s, uint64_t *d_surv, uin
     a.num_instances = b->num_instances;
     a.max_rs = b->max_row_words;
     a.max_kp = b->max_kp;
-    // persistent workgroups reserve output slots in chunks (few global
-    // atomics); one-shot workgroups of the plain mode reserve exactly
-    a.chunk = (s->mode == WPM_SCHED_PLAIN) ? 0 : 128;
+    a.split = 0;
     const dim3 block((unsigned)s->wg_size);
+    // One launch of each kernel the batch needs over [item_base, num_items);
+    // each takes the items of its tables (malformed items are counted once).
+    // Persistent workgroups reserve record slots in blocks of at most 128 per
+    // wave (few global atomics); the one-shot ones of the plain mode reserve
+    // exactly.
+    // (the length of the items, by a look at some of them: parts are not
+    // made shorter than the descent splits)
+    uint64_t item_len = 0;
+    if (s->h_items && s->mode != WPM_SCHED_PLAIN)
+        for (int64_t i = 0; i < s->num_items; i += std::max<int64_t>(1, s->num_items / 32)) {
+            const wpm_item &im = s->h_items[i];
+            if (im.cbits <= WPM_MAX_K - 10) item_len = std::max(item_len, (uint64_t)im.lanes << im.cbits);
+        }
+    auto launch = [&](int64_t want_grid) -> hipError_t {
+        if (tree) {
+            KArgs t = a;
+            int64_t grid = want_grid;
+            t.chunk = (s->mode == WPM_SCHED_PLAIN) ? 0 : 2 * (uint64_t)s->wg_size;
+            t.count_bad = !walk;
+            t.alone = !walk;
+            if (t.mode == 1 || t.mode == 2) {
+                // Fewer items than workgroups: hand each out in parts (stamped
+                // items stay whole).  No workgroup without work.
+                if (!t.times)
+                    while (t.split < 6 && item_len >> (t.split + 1) >= (uint64_t)TREE_MIN_SPLIT &&
+                           (t.num_items << (t.split + 1)) <= grid)
+                        ++t.split;
+                const int64_t parts = t.num_items << t.split;
+                grid = std::min<int64_t>(grid, parts);
+            }
+            const hipError_t e = launch_tree(dim3((unsigned)grid), block, tree_lds, st, b->d_tables, b->d_offsets,
+                                             s->d_items, t);
+            if (e != hipSuccess) return e;
+        }
+        if (walk) {
+            KArgs w = a;
+            w.chunk = (s->mode == WPM_SCHED_PLAIN) ? 0 : 128;
+            w.count_bad = 1;
+            w.alone = !tree;
+            w.head = a.head ? a.head + 1 : nullptr;
+            const int64_t grid = w.mode == 3 ? want_grid : std::min<int64_t>(want_grid, w.num_items - w.item_base);
+            return launch_sweep(waves, dim3((unsigned)grid), block, lds, st, b->d_tables, b->d_offsets, s->d_items, w);
+        }
+        return hipSuccess;
+    };
     if (s->mode == WPM_SCHED_PLAIN) {
         // One launch per instance: a grid of exactly that instance's items
         // (items naming an unknown instance are rejected before any launch;
@@ -158,9 +212,7 @@ int enumerate_with(const wpm_batch *b, const wpm_sched *s, uint64_t *d_surv, uin
             while (e < s->num_items && s->h_items[e].instance == s->h_items[i].instance) ++e;
             a.item_base = i;
             a.num_items = e;
-            const int64_t nb = e - i;
-            HIP_TRY(launch_sweep(waves, dim3((unsigned)nb), block, lds, st, b->d_tables, b->d_offsets,
-                                 s->d_items, a));
+            HIP_TRY(launch(e - i));
             i = e;
         }
         return WPM_OK;
@@ -168,8 +220,7 @@ int enumerate_with(const wpm_batch *b, const wpm_sched *s, uint64_t *d_surv, uin
     int32_t grid = s->grid;
     if (grid <= 0 && (rc = persistent_grid_waves(b, s->wg_size, waves, &grid))) return rc;
     a.mode = (s->mode == WPM_SCHED_STATIC) ? 1 : (s->mode == WPM_SCHED_DYNAMIC) ? 2 : 3;
-    HIP_TRY(launch_sweep(waves, dim3((unsigned)grid), block, lds, st, b->d_tables, b->d_offsets,
-                         s->d_items, a));
+    HIP_TRY(launch(grid));
     return WPM_OK;
 }
 

@@ -32,13 +32,23 @@ enum {
     HDR_MAXF = 8,
     HDR_NCRIT = 9,
     HDR_NFILT = 10,
-    HDR_FLAGS = 11,   // bit 0: row kp holds the offset K* of an affine coset
+    HDR_FLAGS = 11,   // bit 0: row kp holds the offset K* of an affine coset; bit 1: level section
     HDR_PROPS = 12,   // word offset of the property section (0: none)
     HDR_NPROPS = 13,  // affine properties besides the facet bound
     HDR_DEFER = 14,   // word offset of the deferred-ridge section (0: none)
     HDR_NDEFER = 15,  // deferred ridges: checked after the resident groups
 };
 constexpr uint32_t HDR_FLAG_OFFSET = 1;
+constexpr uint32_t HDR_FLAG_TREE = 2;
+// Level section: 4-word groups of at most 32 ridges each.
+constexpr int LV_LEAF = 0;      // every vector of a 64-vector sub-cube
+constexpr int LV_SIX = 4;       // 64-vector sub-cubes, two groups
+constexpr int LV_TWELVE = 12;   // 4096-vector sub-cubes
+constexpr int LV_EIGHTEEN = 16; // 2^18-vector sub-cubes
+constexpr int WPM_LEVEL_WORDS = 20;
+// Instances that get a level section.
+constexpr int WPM_TREE_SMALL_K = 16;
+constexpr double WPM_TREE_MAX_PASS = 0.75;
 
 struct Incidence {
     int n = 0, M = 0, N = 0;

@@ -29,6 +29,27 @@
 
 namespace wpm {
 
+// Population counts over sample words, with the popcnt instruction where the
+// host has it (the greedy ridge rankings spend most of packing in them; the
+// baseline x86-64 code for a 64-bit count is a dozen operations).
+#if defined(__x86_64__) && !defined(__HIP_DEVICE_COMPILE__)
+#define WPM_POPCNT __attribute__((target_clones("popcnt", "default")))
+#else
+#define WPM_POPCNT
+#endif
+// bits of a[w] & b[w] over the listed words
+WPM_POPCNT int count_common(const uint64_t *a, const uint64_t *b, const int32_t *words, size_t n) {
+    int s = 0;
+    for (size_t i = 0; i < n; ++i) s += __builtin_popcountll(a[words[i]] & b[words[i]]);
+    return s;
+}
+// bits of a[0..n)
+WPM_POPCNT int64_t count_bits(const uint64_t *a, size_t n) {
+    int64_t s = 0;
+    for (size_t i = 0; i < n; ++i) s += __builtin_popcountll(a[i]);
+    return s;
+}
+
 namespace {
 
 inline uint32_t rev32(uint32_t x) {
@@ -237,6 +258,90 @@ namespace {
 
 int slot_stride_for(int q) { return q <= 4 ? 4 : 8; }
 
+// ---- sub-cube tests (the tree descent of the sweep kernel)
+//
+// Let the low L coordinates of x run freely.  A facet whose basis membership
+// has none of those bits is constant over the sub-cube of 2^L vectors.  If at
+// least 3 of up to 4 constant parents of a ridge are in K, the ridge has
+// degree >= 3, hence (even degrees) >= 4, for every vector of the sub-cube, and
+// Proposition 2.1 rejects all of them at once.  For a ridge with at most 5
+// parents, all constant, the test is exact.
+struct LevelRidge {
+    int c;            // index into the critical ridges
+    int np;           // constant parents used, 3 or 4
+    int32_t par[4];   // their facets
+};
+
+// Ridges whose test applies to sub-cubes of 2^L vectors.
+std::vector<LevelRidge> level_ridges(const Incidence &inc, const std::vector<int32_t> &crit,
+                                     const std::vector<uint64_t> &frow, int L) {
+    const uint64_t low = (1ull << L) - 1;
+    std::vector<LevelRidge> out;
+    for (int c = 0; c < (int)crit.size(); ++c) {
+        const int r = crit[c];
+        LevelRidge lr{c, 0, {0, 0, 0, 0}};
+        for (int q = inc.parent_off[r]; q < inc.parent_off[r + 1] && lr.np < 4; ++q)
+            if (!(frow[inc.parents[q]] & low)) lr.par[lr.np++] = inc.parents[q];
+        if (lr.np >= 3) out.push_back(lr);
+    }
+    return out;
+}
+
+// At most `most` of the ridges, greedily by the samples each rejects among
+// those still alive (`col(j)` = membership words of facet j over tw sample
+// words); once no ridge rejects any, the rest by their own rejections.
+template <class Col>
+std::vector<LevelRidge> pick_level(const std::vector<LevelRidge> &all, int most, int tw, Col col,
+                                   std::vector<uint64_t> &alive) {
+    const int n = (int)all.size();
+    std::vector<uint64_t> fail((size_t)n * tw);
+    std::vector<int> solo(n, 0);
+    for (int c = 0; c < n; ++c) {
+        const uint64_t *a = col(all[c].par[0]), *b = col(all[c].par[1]), *e = col(all[c].par[2]);
+        const uint64_t *d = all[c].np == 4 ? col(all[c].par[3]) : nullptr;
+        uint64_t *f = fail.data() + (size_t)c * tw;
+        for (int w = 0; w < tw; ++w) {
+            const uint64_t ab = a[w] & b[w], ed = d ? e[w] & d[w] : 0ull, od = d ? e[w] | d[w] : e[w];
+            f[w] = (ab & od) | (ed & (a[w] | b[w]));  // at least 3 of the 4 (or all 3)
+        }
+        solo[c] = (int)count_bits(f, (size_t)tw);
+    }
+    std::vector<int32_t> aw;
+    for (int w = 0; w < tw; ++w)
+        if (alive[w]) aw.push_back(w);
+    std::vector<char> used(n, 0);
+    std::vector<LevelRidge> out;
+    while ((int)out.size() < most) {
+        int best = -1, best_gain = -1;
+        for (int c = 0; c < n; ++c) {
+            if (used[c]) continue;
+            const int g = count_common(fail.data() + (size_t)c * tw, alive.data(), aw.data(), aw.size());
+            if (g > best_gain || (g == best_gain && g == 0 && solo[c] > solo[best])) {
+                best = c;
+                best_gain = g;
+            }
+        }
+        if (best < 0) break;
+        used[best] = 1;
+        out.push_back(all[best]);
+        const uint64_t *f = fail.data() + (size_t)best * tw;
+        size_t keep = 0;
+        for (int32_t w : aw) {
+            alive[w] &= ~f[w];
+            if (alive[w]) aw[keep++] = w;
+        }
+        aw.resize(keep);
+    }
+    return out;
+}
+
+// The ridges of the tree descent, and the share of 64-vector sub-cubes that
+// the tests of 12 and 6 free coordinates leave.
+struct LevelPlan {
+    std::vector<LevelRidge> leaf, six, twelve, eighteen;
+    double pass6 = 1.0;
+};
+
 }  // namespace
 
 int pack_instance(int n, int m, const uint32_t *facets, int32_t M, const uint32_t *basis,
@@ -406,6 +511,55 @@ int pack_instance(int n, int m, const uint32_t *facets, int32_t M, const uint32_
             fc[TW - 1] &= tail_mask;
         }
     }
+    // Tree descent: ridges for sub-cubes of 2^18, 2^12 and 2^6 vectors, ranked on the
+    // first samples, then the leaf ridges, ranked on all 64 vectors of the
+    // sub-cubes that pass (sample words: one sub-cube each, bit r = its vector
+    // with low coordinates r).
+    LevelPlan lv;
+    bool tree = k <= WPM_TREE_SMALL_K;
+    {
+        const int tw = std::min(TW, 256);
+        auto col = [&](int32_t j) -> const uint64_t * { return cols.data() + (size_t)fcol[j] * TW; };
+        std::vector<uint64_t> up(tw, ~0ull);
+        if (tw == TW) up[tw - 1] = tail_mask;
+        const int64_t up0 = count_bits(up.data(), up.size());
+        lv.eighteen = pick_level(level_ridges(inc, crit, frow, 18), 32, tw, col, up);
+        lv.twelve = pick_level(level_ridges(inc, crit, frow, 12), 32, tw, col, up);
+        lv.six = pick_level(level_ridges(inc, crit, frow, 6), 64, tw, col, up);
+        lv.pass6 = (double)count_bits(up.data(), up.size()) / (double)up0;
+        tree = tree || lv.pass6 <= WPM_TREE_MAX_PASS;
+        if (tree) {
+            std::vector<int32_t> cube;  // samples of sub-cubes that pass (any, when none does)
+            for (int w = 0; w < tw; ++w)
+                for (uint64_t b = up[w]; b && cube.size() < 128; b &= b - 1)
+                    cube.push_back(w * 64 + __builtin_ctzll(b));
+            if (cube.empty())
+                for (int q = 0; q < std::min(T, 64); ++q) cube.push_back(q);
+            const int cw = (int)cube.size();
+            static const uint64_t bitpat[6] = {0xAAAAAAAAAAAAAAAAull, 0xCCCCCCCCCCCCCCCCull,
+                                               0xF0F0F0F0F0F0F0F0ull, 0xFF00FF00FF00FF00ull,
+                                               0xFFFF0000FFFF0000ull, 0xFFFFFFFF00000000ull};
+            std::vector<uint64_t> xlow(cw, 0);  // low coordinates of the samples themselves
+            for (int t = 0; t < std::min(k, 6); ++t)
+                for (int q = 0; q < cw; ++q)
+                    xlow[q] |= ((X[(size_t)t * TW + cube[q] / 64] >> (cube[q] % 64)) & 1ull) << t;
+            std::vector<uint64_t> cc((size_t)std::max(nf, 1) * cw);
+            for (int j = 0; j < M; ++j) {
+                if (fcol[j] < 0) continue;
+                const uint64_t fl = frow[j] & 63u, *cj = col(j);
+                uint64_t pat = 0;
+                for (uint64_t b = fl; b; b &= b - 1) pat ^= bitpat[__builtin_ctzll(b)];
+                for (int q = 0; q < cw; ++q) {
+                    const uint64_t own = (cj[cube[q] / 64] >> (cube[q] % 64)) & 1ull;
+                    const uint64_t base = own ^ (uint64_t)(__builtin_popcountll(fl & xlow[q]) & 1);
+                    cc[(size_t)fcol[j] * cw + q] = pat ^ (0ull - base);
+                }
+            }
+            std::vector<uint64_t> all(cw, ~0ull);
+            lv.leaf = pick_level(level_ridges(inc, crit, frow, 0), 32, cw,
+                                 [&](int32_t j) -> const uint64_t * { return cc.data() + (size_t)fcol[j] * cw; }, all);
+        }
+    }
     std::vector<uint64_t>().swap(cols);
     std::vector<uint64_t>().swap(X);
     // Greedy ordering: repeatedly take the ridge that rejects the most samples
@@ -419,9 +573,7 @@ int pack_instance(int n, int m, const uint32_t *facets, int32_t M, const uint32_
     for (int w = 0; w < TW; ++w) aw[w] = w;
     std::vector<int> solo(n_crit, 0);
     for (int c = 0; c < n_crit; ++c) {
-        int s = 0;
-        for (int w = 0; w < TW; ++w) s += __builtin_popcountll(fail[(size_t)c * TW + w]);
-        solo[c] = s;
+        solo[c] = (int)count_bits(fail.data() + (size_t)c * TW, (size_t)TW);
     }
     std::vector<char> used(n_crit, 0);
     auto greedy_pick = [&](bool need_small) -> int {
@@ -432,9 +584,7 @@ int pack_instance(int n, int m, const uint32_t *facets, int32_t M, const uint32_
             const int pr = inc.parent_off[r + 1] - inc.parent_off[r];
             if (need_small && pr > 5) continue;
             if (pr - 1 > WPM_MAX_SLOTS) continue;  // too many parents to be resident
-            int g = 0;
-            const uint64_t *fc = fail.data() + (size_t)c * TW;
-            for (int w : aw) g += __builtin_popcountll(fc[w] & alive[w]);
+            const int g = count_common(fail.data() + (size_t)c * TW, alive.data(), aw.data(), aw.size());
             if (g > best_gain || (g == best_gain && g == 0 && solo[c] > solo[best])) {
                 best = c;
                 best_gain = g;
@@ -487,7 +637,8 @@ int pack_instance(int n, int m, const uint32_t *facets, int32_t M, const uint32_
     const int kp = std::max(k, 7);
     const int RS = ((4 + (G - 1) * QS + W) + 3) & ~3;
     const int nrows = kp + (offset ? 1 : 0);  // the offset row follows the basis rows
-    const int64_t props_at = (int64_t)WPM_HDR_WORDS + (int64_t)nrows * RS;
+    const int64_t level_at = (int64_t)WPM_HDR_WORDS + (int64_t)nrows * RS;
+    const int64_t props_at = level_at + (tree ? (int64_t)nrows * WPM_LEVEL_WORDS : 0);
     const int64_t defer_at = props_at + (nprops ? 2 * (int64_t)nprops + (int64_t)nclasses * (1 + W) : 0);
     const int64_t words = defer_at + defer_words;
 
@@ -523,7 +674,7 @@ int pack_instance(int n, int m, const uint32_t *facets, int32_t M, const uint32_
     h[HDR_MAXF] = (uint32_t)max_facets;
     h[HDR_NCRIT] = (uint32_t)n_crit;
     h[HDR_NFILT] = (uint32_t)filt.size();
-    h[HDR_FLAGS] = offset ? HDR_FLAG_OFFSET : 0u;
+    h[HDR_FLAGS] = (offset ? HDR_FLAG_OFFSET : 0u) | (tree ? HDR_FLAG_TREE : 0u);
     h[HDR_PROPS] = nprops ? (uint32_t)props_at : 0u;
     h[HDR_NPROPS] = (uint32_t)nprops;
     h[HDR_DEFER] = deferred.empty() ? 0u : (uint32_t)defer_at;
@@ -568,6 +719,31 @@ int pack_instance(int n, int m, const uint32_t *facets, int32_t M, const uint32_
         for (int w = 0; w < W; ++w) rows[(size_t)t * RS + koff + w] = basis[(size_t)t * W + w];
     if (offset)
         for (int w = 0; w < W; ++w) rows[(size_t)kp * RS + koff + w] = offset[w];
+    // level section: the sub-cube tests' slot words of every row
+    if (tree) {
+        uint32_t *lrows = table + level_at;
+        auto place_level = [&](const std::vector<LevelRidge> &lr, size_t from, int word_base) {
+            for (size_t i = from; i < std::min(lr.size(), from + 32); ++i) {
+                const uint32_t bit = 1u << (i - from);
+                for (int q = 0; q < lr[i].np; ++q) {
+                    const int32_t f = lr[i].par[q];
+                    for (uint64_t b = frow[f]; b; b &= b - 1)
+                        lrows[(size_t)__builtin_ctzll(b) * WPM_LEVEL_WORDS + word_base + q] |= bit;
+                    if (offj[f]) lrows[(size_t)kp * WPM_LEVEL_WORDS + word_base + q] |= bit;
+                }
+            }
+            for (int t = 0; t < nrows; ++t) {
+                uint32_t *r = lrows + (size_t)t * WPM_LEVEL_WORDS + word_base;
+                r[1] ^= r[0];
+                r[3] ^= r[2];
+            }
+        };
+        place_level(lv.leaf, 0, LV_LEAF);
+        place_level(lv.six, 0, LV_SIX);
+        place_level(lv.six, 32, LV_SIX + 4);
+        place_level(lv.twelve, 0, LV_TWELVE);
+        place_level(lv.eighteen, 0, LV_EIGHTEEN);
+    }
     // property section: c0, class count, then (weight, W mask words) per class
     uint32_t *pr = table + props_at;
     for (int q = 0, cls = 0; q < nprops; ++q) {

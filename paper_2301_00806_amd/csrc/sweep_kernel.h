@@ -1,4 +1,6 @@
-// The Gray-code sweep of the F2 kernel on gfx950 (device code).
+// The Gray-code walk of the F2 kernel on gfx950 (device code): it visits
+// every vector.  Instances whose tables have a level section are swept by
+// tree descent instead (tree_kernel.h), which shares the final checks here.
 //
 // Every lane owns a chunk of 2^c consecutive Gray indices i of one instance
 // and visits x = i ^ (i >> 1), so consecutive vectors differ in the single
@@ -62,6 +64,7 @@ enum {
 };
 constexpr uint32_t D_TABLE_MAGIC = 0x314D5057u;  // "WPM1", written by the packer
 constexpr uint32_t D_FLAG_OFFSET = 1;  // row kp holds the offset K* of an affine coset
+constexpr uint32_t D_FLAG_TREE = 2;    // the table has a level section
 
 // Lane offsets d inside an item's aligned window of 2^LANE_BITS chunks:
 // the Gray code of d << c is (d ^ (d << 1)) << (c - 1), LANE_BITS + 1 bits.
@@ -89,7 +92,9 @@ struct KArgs {
     int mode;  // 0 direct (one item per workgroup), 1 static stride, 2 dynamic queue, 3 packed bins
     int num_instances;
     int max_rs, max_kp;  // the LDS of a workgroup holds tables up to these sizes
-    int pad;
+    int count_bad;       // malformed items are counted by this launch
+    int alone;           // no launch of the other kernel: its items are malformed
+    int split;           // descent: every item is handed out as 2^split parts
 };
 
 // Per ridge bit: at least 3 of the slot bits (a, b, c, d) set, given the
@@ -145,6 +150,109 @@ template <class T>
 __device__ __forceinline__ const T *opaque(const T *p) {
     asm volatile("" : "+s"(p));
     return p;
+}
+
+// Tables are in global memory: said so where a pointer has gone through
+// opaque() or LDS (a flat access would also hold up the LDS counter).
+typedef const __attribute__((address_space(1))) uint32_t *gword_ptr;
+__device__ __forceinline__ uint32_t gword(const uint32_t *p) { return *(gword_ptr)p; }
+
+// A wave-uniform table word, loaded where it is used.
+__device__ __forceinline__ uint32_t uword(const uint32_t *q) {
+    return __builtin_amdgcn_readfirstlane(gword(opaque(q)));
+}
+
+// A wave-uniform header field of the table, likewise.
+__device__ __forceinline__ uint32_t hword(const uint32_t *tab, int i) {
+    return __builtin_amdgcn_readfirstlane(gword(opaque(tab) + i));
+}
+
+// Ridge groups g0, g0 + 1, ... of the entries still passing, in decreasing
+// rejection order, stopping once no entry of the wave passes.  word4(off)
+// gives four consecutive state words of the lane's entry, head(i) a field of
+// the table's header.
+template <class H, class W4>
+__device__ __forceinline__ bool groups_pass(H head, bool pass, int g0, W4 word4) {
+    const int Gp = (int)head(D_G), Qs = (int)head(D_QS);
+#pragma unroll 1
+    for (int g = g0; g < Gp; ++g) {
+        if (__builtin_amdgcn_ballot_w64(pass) == 0) break;
+        const int off = g == 0 ? 0 : 4 + (g - 1) * Qs;
+        const uint4 v = word4(off);
+        uint32_t fl;
+        if (Qs == 4 || g == 0) {
+            fl = fail4(v.x, v.y, v.z, v.w);
+        } else {
+            // up to 8 plain slot words: at least 3 set
+            const uint4 v2 = word4(off + 4);
+            const uint32_t sw[8] = {v.x, v.y, v.z, v.w, v2.x, v2.y, v2.z, v2.w};
+            uint32_t c1 = sw[0], c2 = 0, c3 = 0;
+#pragma unroll
+            for (int q = 1; q < 8; ++q) {
+                c3 |= c2 & sw[q];
+                c2 |= c1 & sw[q];
+                c1 |= sw[q];
+            }
+            fl = c3;
+        }
+        pass = pass && fl == 0u;
+    }
+    return pass;
+}
+
+// What the resident ridges leave: the facet count |K| (the upper-bound
+// property of Section 4.2), further affine properties
+// g(K) = c0 + sum_c w_c |K & mask_c| > 0 (Section 2.1) and the deferred ridges
+// (degree <= 2 read off the facet words: parent count, then the parents'
+// facet indices, per ridge).
+template <class H, class W4, class W1>
+__device__ __forceinline__ bool properties_pass(const uint32_t *tab, H head, bool pass, W4 word4, W1 word1) {
+    const int Wp = (int)head(D_W), ko = 4 + ((int)head(D_G) - 1) * (int)head(D_QS);
+    uint32_t cntf = 0;
+#pragma unroll 1
+    for (int w = 0; w < Wp; w += 4) {
+        const uint4 v = word4(ko + w);
+        cntf += __builtin_popcount(v.x) + __builtin_popcount(v.y) + __builtin_popcount(v.z) +
+                __builtin_popcount(v.w);
+    }
+    const uint32_t mf = head(D_MAXF);
+    bool ok = pass && (mf == 0u || cntf <= mf);
+    const uint32_t np = head(D_NPROPS);
+    if (np != 0u && __builtin_amdgcn_ballot_w64(ok) != 0) {
+        const uint32_t *pr = tab + head(D_PROPS);
+#pragma unroll 1
+        for (uint32_t q = 0; q < np; ++q) {
+            int64_t gv = (int32_t)uword(pr);
+            const uint32_t ncls = uword(pr + 1);
+            pr += 2;
+#pragma unroll 1
+            for (uint32_t cl = 0; cl < ncls; ++cl) {
+                uint32_t sum = 0;
+#pragma unroll 1
+                for (int w = 0; w < Wp; ++w) sum += __builtin_popcount(word1(ko + w) & uword(pr + 1 + w));
+                gv += (int64_t)(int32_t)uword(pr) * (int64_t)sum;
+                pr += 1 + Wp;
+            }
+            ok = ok && gv > 0;
+        }
+    }
+    const uint32_t nd = head(D_NDEFER);
+    if (nd != 0u && __builtin_amdgcn_ballot_w64(ok) != 0) {
+        const uint32_t *dr = tab + head(D_DEFER);
+#pragma unroll 1
+        for (uint32_t q = 0; q < nd; ++q) {
+            const uint32_t p = uword(dr);
+            uint32_t deg = 0;
+#pragma unroll 1
+            for (uint32_t j = 0; j < p; ++j) {
+                const uint32_t f = uword(dr + 1 + j);
+                deg += (word1(ko + (int)(f >> 5)) >> (f & 31u)) & 1u;
+            }
+            ok = ok && deg <= 2u;
+            dr += 1 + p;
+        }
+    }
+    return ok;
 }
 
 // Occupancy: the kernel is compiled for WAVES waves per SIMD.  Its state is
@@ -216,7 +324,8 @@ void sweep_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict
         // [7, kp], lanes outside [1, workgroup], chunks beyond 2^kp, or a lane
         // window crossing an aligned group of 2^LANE_BITS chunks) is skipped
         // and counted; the caller sees it in d_total.
-        bool bad = inst >= (uint32_t)a.num_instances;
+        // Items of tables with a level section belong to the descent.
+        bool bad = inst >= (uint32_t)a.num_instances, skip = false;
         const uint32_t *__restrict__ tab = tables;
         int kp = 7, W = 0, G = 1, RS = 4, Qp = 4;
         bool has_off = false;
@@ -228,13 +337,15 @@ void sweep_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict
             Qp = (int)tab[D_QS];
             RS = (int)tab[D_RS];
             has_off = (tab[D_FLAGS] & D_FLAG_OFFSET) != 0u;
-            bad = tab[D_MAGIC] != D_TABLE_MAGIC || kp < 7 || kp > a.max_kp || RS > a.max_rs || (RS & 3) ||
+            skip = (tab[D_FLAGS] & D_FLAG_TREE) != 0u;
+            bad = skip && a.alone;
+            bad = bad || tab[D_MAGIC] != D_TABLE_MAGIC || kp < 7 || kp > a.max_kp || RS > a.max_rs || (RS & 3) ||
                   G < 1 || (Qp != 4 && Qp != 8) || 4 + (G - 1) * Qp + W > RS || c < 7 || c > kp ||
                   lanes < 1 || lanes > bd || (int)(first & ((1u << LANE_BITS) - 1)) + lanes > (1 << LANE_BITS) ||
                   first + (uint64_t)lanes > (1ull << (kp - c));
         }
-        if (bad) {
-            if (tid_now() == 0) {
+        if (bad || skip) {
+            if (bad && a.count_bad && tid_now() == 0) {
                 atomicAdd(a.total + TOT_BAD_ITEMS, 1ull);
                 if (a.times) a.times[2 * it] = a.times[2 * it + 1] = 0;
             }
@@ -379,8 +490,6 @@ void sweep_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict
             // opaque pointer (scalar cache) rather than held in scalar
             // registers through phase 1.
             auto hv = [&](int i) -> uint32_t { return __builtin_amdgcn_readfirstlane(opaque(tab)[i]); };
-            // a wave-uniform table word at a computed address
-            auto uw = [](const uint32_t *q) -> uint32_t { return __builtin_amdgcn_readfirstlane(*opaque(q)); };
             auto iv = [&]() -> wpm_item { return *opaque(items + rfl64((uint64_t)it)); };
             for (uint64_t blk = 0; blk < nblk; ++blk) {
                 // ---- phase 1: fast filter over 64 Gray steps, run as NC
@@ -526,30 +635,9 @@ void sweep_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict
                                 const wpm_item ci = iv();
                                 bool pass = base + ln < cnt &&
                                             wbase + (int)own < (int)__builtin_amdgcn_readfirstlane((uint32_t)ci.lanes);
-                                const int Gp = (int)hv(D_G), Qs = (int)hv(D_QS);
-#pragma unroll 1
-                                for (int g = 1; g < Gp; ++g) {
-                                    if (__builtin_amdgcn_ballot_w64(pass) == 0) break;
-                                    const int off = 4 + (g - 1) * Qs;
-                                    const uint4 v = word4(lo, so, off);
-                                    uint32_t fl;
-                                    if (Qs == 4) {
-                                        fl = fail4(v.x, v.y, v.z, v.w);
-                                    } else {
-                                        // up to 8 plain slot words: at least 3 set
-                                        const uint4 v2 = word4(lo, so, off + 4);
-                                        const uint32_t sw[8] = {v.x, v.y, v.z, v.w, v2.x, v2.y, v2.z, v2.w};
-                                        uint32_t c1 = sw[0], c2 = 0, c3 = 0;
-#pragma unroll
-                                        for (int q = 1; q < 8; ++q) {
-                                            c3 |= c2 & sw[q];
-                                            c2 |= c1 & sw[q];
-                                            c1 |= sw[q];
-                                        }
-                                        fl = c3;
-                                    }
-                                    pass = pass && fl == 0u;
-                                }
+                                auto w4 = [&](int off) { return word4(lo, so, off); };
+                                auto w1 = [&](int off) { return word1(lo, so, off); };
+                                pass = groups_pass(hv, pass, 1, w4);
                                 // Gray index of the owner's step (the chunk
                                 // start is recomputed, not held through phase 1)
                                 const uint64_t f0 = rfl64(ci.first);
@@ -561,56 +649,7 @@ void sweep_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict
                                 const bool offs = (hv(D_FLAGS) & D_FLAG_OFFSET) != 0u;
                                 pass = pass && (x != 0 || offs) && (kk >= 64 || (x >> kk) == 0);
                                 if (__builtin_amdgcn_ballot_w64(pass)) {
-                                    const int Wp = (int)hv(D_W), ko = 4 + (Gp - 1) * Qs;
-                                    uint32_t cntf = 0;
-#pragma unroll 1
-                                    for (int w = 0; w < Wp; w += 4) {
-                                        const uint4 v = word4(lo, so, ko + w);
-                                        cntf += __builtin_popcount(v.x) + __builtin_popcount(v.y) +
-                                                __builtin_popcount(v.z) + __builtin_popcount(v.w);
-                                    }
-                                    const uint32_t mf = hv(D_MAXF);
-                                    bool ok = pass && (mf == 0u || cntf <= mf);
-                                    // further affine properties g(K) = c0 + sum_c w_c |K & mask_c| > 0
-                                    const uint32_t np = hv(D_NPROPS);
-                                    if (np != 0u && __builtin_amdgcn_ballot_w64(ok) != 0) {
-                                        const uint32_t *pr = tab + hv(D_PROPS);
-#pragma unroll 1
-                                        for (uint32_t q = 0; q < np; ++q) {
-                                            int64_t gv = (int32_t)uw(pr);
-                                            const uint32_t ncls = uw(pr + 1);
-                                            pr += 2;
-#pragma unroll 1
-                                            for (uint32_t cl = 0; cl < ncls; ++cl) {
-                                                uint32_t sum = 0;
-#pragma unroll 1
-                                                for (int w = 0; w < Wp; ++w)
-                                                    sum += __builtin_popcount(word1(lo, so, ko + w) & uw(pr + 1 + w));
-                                                gv += (int64_t)(int32_t)uw(pr) * (int64_t)sum;
-                                                pr += 1 + Wp;
-                                            }
-                                            ok = ok && gv > 0;
-                                        }
-                                    }
-                                    // deferred ridges: degree <= 2 in K, read off
-                                    // the facet words (parent count, then the
-                                    // parents' facet indices, per ridge)
-                                    const uint32_t nd = hv(D_NDEFER);
-                                    if (nd != 0u && __builtin_amdgcn_ballot_w64(ok) != 0) {
-                                        const uint32_t *dr = tab + hv(D_DEFER);
-#pragma unroll 1
-                                        for (uint32_t q = 0; q < nd; ++q) {
-                                            const uint32_t p = uw(dr);
-                                            uint32_t deg = 0;
-#pragma unroll 1
-                                            for (uint32_t j = 0; j < p; ++j) {
-                                                const uint32_t f = uw(dr + 1 + j);
-                                                deg += (word1(lo, so, ko + (int)(f >> 5)) >> (f & 31u)) & 1u;
-                                            }
-                                            ok = ok && deg <= 2u;
-                                            dr += 1 + p;
-                                        }
-                                    }
+                                    const bool ok = properties_pass(tab, hv, pass, w4, w1);
                                     const uint64_t pball = __builtin_amdgcn_ballot_w64(pass);
                                     const uint64_t bal = __builtin_amdgcn_ballot_w64(ok);
                                     bk.n_ridge += (uint32_t)__builtin_popcountll(pball);

@@ -312,6 +312,12 @@ def lds_class(info) -> int:
     return next(c for c in LDS_CLASSES if info.row_words <= c)
 
 
+def _sweep_kind(members) -> int:
+    """wpm_batch flags: whether all tables, or none, have a level section."""
+    kinds = {bool(int(p.table[11]) & 2) for p in members}
+    return L.BATCH_TREE if kinds == {True} else L.BATCH_WALK if kinds == {False} else 0
+
+
 class DeviceBatch:
     """Packed tables of a list of prepared instances, resident in HBM."""
 
@@ -358,7 +364,8 @@ class DeviceBatch:
             max_slots=max([p.info.slots for p in members] + [4]),
             max_words=max([p.info.W for p in members] + [1]),
             max_kp=max([max(p.k, 7) for p in members] + [7]),
-            d_tables=self.tables.data_ptr(), d_offsets=self.offsets.data_ptr(), flags=0)
+            d_tables=self.tables.data_ptr(), d_offsets=self.offsets.data_ptr(),
+            flags=_sweep_kind(members))
 
     @property
     def vectors(self) -> int:

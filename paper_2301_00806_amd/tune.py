@@ -34,9 +34,11 @@ def shape_key(batch: "E.DeviceBatch") -> str:
     import torch
     arch = torch.cuda.get_device_properties(0).gcnArchName.split(":")[0]
     b = batch.c_batch
-    src = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc", "sweep_kernel.h")
-    with open(src, "rb") as f:
-        kh = hashlib.sha256(f.read()).hexdigest()[:12]
+    h = hashlib.sha256()
+    for name in ("sweep_kernel.h", "tree_kernel.h"):
+        with open(os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc", name), "rb") as f:
+            h.update(f.read())
+    kh = h.hexdigest()[:12]
     lv = int(np.log2(max(1.0, batch.visited / max(1, len(batch.preps)))))
     pr = "/pruned" if batch.blocks is not None else ""
     return f"{arch}/{kh}/rs{b.max_row_words}/v{lv}{pr}"

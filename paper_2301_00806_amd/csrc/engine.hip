@@ -4,11 +4,15 @@
 #include <algorithm>
 #include <atomic>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <memory>
 #include <mutex>
+#include <new>
 #include <thread>
 #include <vector>
+
+#include <sys/mman.h>
 
 #include "internal.h"
 #include "launch.h"
@@ -272,49 +276,140 @@ int enumerate_noalloc(const wpm_batch *b, const wpm_sched *s, uint64_t *d_surv, 
 
 namespace {
 
-// Run fn(i) for i in [0, num) on up to 16 host threads (dynamic chunks of
-// `grain`).
-template <class Fn>
-void host_parallel_for(int64_t num, Fn fn, int64_t grain = 16) {
-    const int hw = (int)std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
-    const int nt = (int)std::min<int64_t>(hw, std::max<int64_t>(1, (num + grain - 1) / grain));
-    std::atomic<int64_t> next{0};
-    auto work = [&]() {
+// The threads of one call: the calling one and up to 15 more run the same
+// function, phase by phase, with a barrier between phases.  (Threads started
+// and joined for each phase cost more than the phases of a small result.)
+// Threads start each other as a tree: one thread starting 15 took 200 us.
+class Team {
+   public:
+    // fn(t) on `want` threads (fewer if the system refuses some).
+    template <class Fn>
+    void run(int want, Fn fn) {
+        grow(0, want, fn);
+        // (threads start counting in before fn; refused ones are counted out)
+        while (size_.load(std::memory_order_acquire) == 0) {
+            const int n = started_.load(std::memory_order_acquire);
+            if (n + refused_.load(std::memory_order_acquire) == want) size_.store(n, std::memory_order_release);
+            std::this_thread::yield();
+        }
+        fn(0);
+        for (int t = 1; t < MAX; ++t)
+            if (th_[t].joinable()) th_[t].join();
+    }
+    void barrier() {
+        const int g = gen_.load(std::memory_order_acquire);
+        if (arrived_.fetch_add(1, std::memory_order_acq_rel) + 1 == size_.load(std::memory_order_relaxed)) {
+            arrived_.store(0, std::memory_order_relaxed);
+            gen_.store(g + 1, std::memory_order_release);
+        } else {
+            for (int i = 0; gen_.load(std::memory_order_acquire) == g; ++i)
+                if (i > 256) std::this_thread::yield();
+        }
+    }
+    // this thread's share of [0, num), `grain` at a time (one phase number per loop)
+    template <class Fn>
+    void share(int phase, int64_t num, int64_t grain, Fn fn) {
         for (;;) {
-            const int64_t a = next.fetch_add(grain);
+            const int64_t a = next_[phase].fetch_add(grain, std::memory_order_relaxed);
             if (a >= num) break;
             for (int64_t i = a; i < std::min(num, a + grain); ++i) fn(i);
         }
-    };
-    std::vector<std::thread> th;
-    for (int t = 1; t < nt; ++t) th.emplace_back(work);
-    work();
-    for (auto &t : th) t.join();
-}
+    }
 
-// One instance's facets in increasing vertex-mask order, and its basis (and
-// coset offset) with the facet bits moved to those positions: the set bits of
-// a complex's bit vector, read in increasing position, are then its facets in
-// increasing mask order.
-struct SortedFacets {
-    int W = 0;
-    std::vector<uint32_t> mask;   // [M] facet masks, increasing
-    std::vector<uint32_t> basis;  // [k][W] permuted basis rows
-    std::vector<uint32_t> off;    // [W] permuted offset (zero for a subspace)
+   private:
+    static constexpr int MAX = 16;
+    // thread t of `want`: starts threads 2t + 1 and 2t + 2.  th_ is written by
+    // the starter alone; the calling thread joins in increasing order, so a
+    // thread's starter has ended, and its th_ entries are there, before it
+    // is looked at.
+    template <class Fn>
+    void grow(int t, int want, Fn &fn) {
+        started_.fetch_add(1, std::memory_order_acq_rel);
+        for (int c = 2 * t + 1; c <= 2 * t + 2 && c < want; ++c) {
+            try {
+                th_[c] = std::thread([this, c, want, &fn] {
+                    grow(c, want, fn);
+                    while (size_.load(std::memory_order_acquire) == 0) std::this_thread::yield();
+                    fn(c);
+                });
+            } catch (...) {
+                refused_.fetch_add(subtree(c, want), std::memory_order_acq_rel);
+            }
+        }
+    }
+    static int subtree(int c, int want) {
+        return c < want ? 1 + subtree(2 * c + 1, want) + subtree(2 * c + 2, want) : 0;
+    }
+    std::thread th_[MAX];
+    std::atomic<int> started_{0}, refused_{0}, size_{0}, arrived_{0}, gen_{0};
+    std::atomic<int64_t> next_[8] = {};
 };
 
-SortedFacets sort_facets(const wpm_host_instance &in) {
-    SortedFacets sf;
-    const int M = in.M, W = (M + 31) / 32;
-    sf.W = W;
-    std::vector<int32_t> order(M);
+// Uninitialised host memory of one call, from 4 MB on in huge pages: the first
+// touch of ordinary pages took longer than the phases that fill them.
+template <class T>
+class Buffer {
+   public:
+    Buffer() = default;
+    ~Buffer() { std::free(p_); }
+    Buffer(const Buffer &) = delete;
+    Buffer &operator=(const Buffer &) = delete;
+    bool reset(size_t n) {
+        constexpr size_t HUGE_PAGE = (size_t)2 << 20;
+        const size_t bytes = std::max<size_t>(1, n) * sizeof(T);
+        std::free(p_);
+        if (bytes >= 2 * HUGE_PAGE) {
+            const size_t whole = (bytes + HUGE_PAGE - 1) & ~(HUGE_PAGE - 1);
+            p_ = (T *)std::aligned_alloc(HUGE_PAGE, whole);
+            if (p_) (void)madvise(p_, whole, MADV_HUGEPAGE);
+        } else {
+            p_ = (T *)std::malloc(bytes);
+        }
+        return p_ != nullptr;
+    }
+    T *get() const { return p_; }
+    T &operator[](size_t i) const { return p_[i]; }
+
+   private:
+    T *p_ = nullptr;
+};
+
+// A key whose order agrees with the canonical order wherever two keys differ:
+// the first 128 positions, facet 0 first, a held facet below a missing one; the
+// positions after a complex's last facet count as held, so that a list that is a
+// prefix of another does not come after it.  Equal keys say nothing.
+struct Key {
+    uint64_t a, b;
+    bool operator<(const Key &o) const { return a != o.a ? a < o.a : b < o.b; }
+    bool operator==(const Key &o) const { return a == o.a && b == o.b; }
+};
+
+// One instance's part of a call: its facets in increasing vertex-mask order,
+// its basis (and coset offset) with the facet bits moved to those positions --
+// the set bits of a complex's bit vector, read in increasing position, are then
+// its facets in increasing mask order -- and the places of its results.
+struct Collected {
+    int W = 0;
+    uint32_t *mask = nullptr;   // [M] facet masks, increasing
+    uint32_t *basis = nullptr;  // [k][W] permuted basis rows
+    uint32_t *off = nullptr;    // [W] permuted offset (zero for a subspace)
+    int64_t first = 0, n = 0;   // results [first, first + n) of the call
+    uint32_t *kv = nullptr;     // [n][W] permuted bit vectors
+    int buckets = 1;            // key ranges the results are sorted in
+    int64_t chunk0 = 0, chunks = 0, bucket0 = 0;
+    Key *split = nullptr;       // [buckets - 1] first keys of the ranges after the first
+    int64_t words = 0;
+};
+
+// (arrays of the right size, zeroed)
+void sort_facets(const wpm_host_instance &in, Collected &c) {
+    const int M = in.M, W = c.W;
+    int32_t order[WPM_MAX_M], pos[WPM_MAX_M];
     for (int j = 0; j < M; ++j) order[j] = j;
-    std::sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return in.facets[a] < in.facets[b]; });
-    std::vector<int32_t> pos(M);
-    sf.mask.resize(M);
+    std::sort(order, order + M, [&](int32_t a, int32_t b) { return in.facets[a] < in.facets[b]; });
     for (int r = 0; r < M; ++r) {
         pos[order[r]] = r;
-        sf.mask[r] = in.facets[order[r]];
+        c.mask[r] = in.facets[order[r]];
     }
     auto permute = [&](const uint32_t *src, uint32_t *dst) {
         for (int w = 0; w < W; ++w)
@@ -323,11 +418,39 @@ SortedFacets sort_facets(const wpm_host_instance &in) {
                 dst[r >> 5] |= 1u << (r & 31);
             }
     };
-    sf.basis.assign((size_t)in.k * W, 0u);
-    for (int t = 0; t < in.k; ++t) permute(in.basis + (size_t)t * W, sf.basis.data() + (size_t)t * W);
-    sf.off.assign((size_t)W, 0u);
-    if (in.offset) permute(in.offset, sf.off.data());
-    return sf;
+    for (int t = 0; t < in.k; ++t) permute(in.basis + (size_t)t * W, c.basis + (size_t)t * W);
+    if (in.offset) permute(in.offset, c.off);
+}
+
+// The complex of x as a permuted bit vector.
+inline void expand(const Collected &c, uint64_t x, uint32_t *K) {
+    for (int q = 0; q < c.W; ++q) K[q] = c.off[q];
+    for (uint64_t b = x; b; b &= b - 1) {
+        const uint32_t *row = c.basis + (size_t)__builtin_ctzll(b) * c.W;
+        for (int q = 0; q < c.W; ++q) K[q] ^= row[q];
+    }
+}
+
+inline uint64_t reverse_bits(uint64_t v) {
+    v = ((v >> 1) & 0x5555555555555555ull) | ((v & 0x5555555555555555ull) << 1);
+    v = ((v >> 2) & 0x3333333333333333ull) | ((v & 0x3333333333333333ull) << 2);
+    v = ((v >> 4) & 0x0F0F0F0F0F0F0F0Full) | ((v & 0x0F0F0F0F0F0F0F0Full) << 4);
+    return __builtin_bswap64(v);
+}
+
+inline Key order_key(const uint32_t *K, int W) {
+    auto two = [&](int q) -> uint64_t {
+        return (q < W ? (uint64_t)K[q] : 0u) | (q + 1 < W ? (uint64_t)K[q + 1] << 32 : 0u);
+    };
+    uint64_t a = two(0), b = two(2);
+    bool later = false;
+    for (int q = 4; q < W && !later; ++q) later = K[q] != 0u;
+    auto fill = [](uint64_t v) { return v ? v | (~0ull << (63 - __builtin_clzll(v))) : ~0ull; };
+    if (!later) {
+        if (!b) a = fill(a);
+        b = fill(b);
+    }
+    return {~reverse_bits(a), ~reverse_bits(b)};
 }
 
 // Canonical order of two complexes given as permuted bit vectors (facets in
@@ -382,123 +505,249 @@ int collect(const wpm_host_instance *insts, int32_t num, const uint64_t *d_surv,
     if (sum != total) return WPM_EINVAL;  // counts and total disagree: corrupted buffers
     // the records: read in place when they are in host memory, else copied
     const uint64_t *rec = d_surv;
-    std::unique_ptr<uint64_t[]> rec_copy;  // uninitialised: the copy fills it
+    Buffer<uint64_t> rec_copy;
     {
         hipPointerAttribute_t attr;
         const bool host = hipPointerGetAttributes(&attr, d_surv) == hipSuccess &&
                           attr.type == hipMemoryTypeHost;
         (void)hipGetLastError();
         if (!host && slots) {
-            rec_copy.reset(new uint64_t[2 * slots]);
+            if (!rec_copy.reset(2 * slots)) return WPM_ELIMIT;
             HIP_TRY(hipMemcpyAsync(rec_copy.get(), d_surv, sizeof(uint64_t) * 2 * slots, hipMemcpyDefault, st));
             HIP_TRY(hipStreamSynchronize(st));
             rec = rec_copy.get();
         }
     }
-    // group the records by instance: per-range histograms, then scatter
-    const int64_t ranges = std::max<int64_t>(1, std::min<int64_t>(64, (int64_t)(slots / 65536) + 1));
+    // Phases, each shared by the team: the records are grouped by instance
+    // (histograms of record ranges, then scatter); every result is expanded
+    // into a permuted bit vector and assigned, in instances with many, to one
+    // of `buckets` key ranges; each bucket is sorted and written.  (By instance
+    // only, with one thread sorting through an index: 23,399 results of one
+    // instance took 3.6 ms, 99,098 of one 3.7 ms, 544,237 of 256 12.5 ms; now
+    // 1.1, 2.4 and 9.5 ms on 16 cores, copy of the records and page faults of
+    // the result included, which bound the last.)
+    const int hw = (int)std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
+    const int want = (int)std::min<int64_t>(hw, 1 + (int64_t)(slots / 1024) + num / 64);
+    const int64_t ranges = std::max<int64_t>(1, std::min<int64_t>(64, (int64_t)(slots / 8192) + 1));
     const uint64_t per = (slots + ranges - 1) / (uint64_t)ranges;
-    std::vector<int64_t> hist((size_t)ranges * (size_t)num, 0);
-    std::atomic<int> bad{0};
-    host_parallel_for(ranges, [&](int64_t r) {
-        int64_t *h = hist.data() + (size_t)r * num;
-        const uint64_t e = std::min<uint64_t>(slots, (uint64_t)(r + 1) * per);
-        for (uint64_t q = (uint64_t)r * per; q < e; ++q) {
-            const uint64_t inst = rec[2 * q + 1];
-            if (inst == ~0ull) continue;
-            if (inst >= (uint64_t)num) { bad = 1; return; }
-            const uint64_t x = rec[2 * q];
-            if (insts[inst].k < 64 && (x >> insts[inst].k)) { bad = 1; return; }
-            ++h[inst];
-        }
-    }, 1);
-    if (bad) return WPM_EINVAL;
-    std::vector<int64_t> start((size_t)num + 1, 0);
-    for (int i = 0; i < num; ++i) {
-        int64_t c = 0;
-        for (int64_t r = 0; r < ranges; ++r) {
-            int64_t &h = hist[(size_t)r * num + i];
-            const int64_t v = h;
-            h = start[i] + c;  // this range's first position for instance i
-            c += v;
-        }
-        if ((uint64_t)c != h_counts[i]) return WPM_EINVAL;
-        start[i + 1] = start[i] + c;
-    }
-    std::unique_ptr<uint64_t[]> xs(new uint64_t[(size_t)std::max<int64_t>(1, start[num])]);
-    host_parallel_for(ranges, [&](int64_t r) {
-        int64_t *h = hist.data() + (size_t)r * num;
-        const uint64_t e = std::min<uint64_t>(slots, (uint64_t)(r + 1) * per);
-        for (uint64_t q = (uint64_t)r * per; q < e; ++q) {
-            const uint64_t inst = rec[2 * q + 1];
-            if (inst != ~0ull) xs[(size_t)h[inst]++] = rec[2 * q];
-        }
-    }, 1);
-    // Per instance: the x values expanded into permuted bit vectors (kept
-    // when the lists are to be written) and the words of its lists, one
-    // length word plus |K| facets per complex.
+    constexpr int64_t CHUNK = 1024;
     const bool write = h_out != nullptr;
-    std::vector<SortedFacets> sfs(write ? (size_t)num : 0);
-    std::vector<std::vector<uint32_t>> kvs(write ? (size_t)num : 0);
-    std::vector<int64_t> iw((size_t)num, 0);
-    host_parallel_for(num, [&](int64_t i) {
-        const int64_t n_i = start[i + 1] - start[i];
-        if (!n_i) return;
-        SortedFacets sf = sort_facets(insts[i]);
-        const int W = sf.W;
-        std::vector<uint32_t> kv((size_t)n_i * (size_t)std::max(W, 1));
-        int64_t w = n_i;
-        for (int64_t r = 0; r < n_i; ++r) {
-            uint32_t *K = kv.data() + (size_t)r * W;
-            for (int q = 0; q < W; ++q) K[q] = sf.off[q];
-            for (uint64_t b = xs[(size_t)(start[i] + r)]; b; b &= b - 1) {
-                const uint32_t *row = sf.basis.data() + (size_t)__builtin_ctzll(b) * W;
-                for (int q = 0; q < W; ++q) K[q] ^= row[q];
-            }
-            for (int q = 0; q < W; ++q) w += __builtin_popcount(K[q]);
-        }
-        iw[(size_t)i] = w;
-        if (write) {
-            sfs[(size_t)i] = std::move(sf);
-            kvs[(size_t)i] = std::move(kv);
-        }
-    });
-    xs.reset();
-    int64_t words = 0;
-    for (int i = 0; i < num; ++i) {
-        h_offsets[i] = words;
-        words += iw[(size_t)i];
+    struct Task { int32_t inst; int32_t sub; };
+    struct Cell { int64_t n, words; };
+    std::vector<int64_t> hist;
+    std::vector<Collected> cs;
+    struct Ref { Key key; int64_t idx; };
+    Buffer<uint64_t> xs;
+    Buffer<Key> keys;
+    Buffer<uint32_t> kv;
+    Buffer<uint8_t> bucket_of;
+    Buffer<Ref> refs;
+    std::vector<uint32_t> facet_words;
+    std::vector<Key> splits;
+    std::vector<Task> chunk_tasks, bucket_tasks;
+    std::vector<int64_t> cell0;   // first cell of each chunk task
+    std::vector<Cell> cells;      // per chunk task and bucket
+    std::vector<Cell> starts;     // per bucket task: first result, first word (in the instance)
+    std::atomic<int> bad{0};
+    int rc = WPM_OK;
+    bool stop = false;
+    try {
+        hist.assign((size_t)ranges * (size_t)num, 0);
+        cs.resize((size_t)num);
+    } catch (const std::bad_alloc &) {
+        return WPM_ELIMIT;
     }
-    h_offsets[num] = words;
-    *out_words = words;
-    if (!write || out_cap < words) return WPM_ECAP;
-    // per instance: canonical sort of the bit vectors, then the facet lists
-    host_parallel_for(num, [&](int64_t i) {
-        const int64_t n_i = start[i + 1] - start[i];
-        if (!n_i) return;
-        const SortedFacets &sf = sfs[(size_t)i];
-        const int W = sf.W;
-        std::vector<uint32_t> &kv = kvs[(size_t)i];
-        std::vector<int64_t> idx((size_t)n_i);
-        for (int64_t r = 0; r < n_i; ++r) idx[(size_t)r] = r;
-        std::sort(idx.begin(), idx.end(), [&](int64_t a, int64_t b) {
-            return canon_less(kv.data() + (size_t)a * W, kv.data() + (size_t)b * W, W);
-        });
-        int64_t w = h_offsets[i];
-        for (int64_t r : idx) {
-            const uint32_t *K = kv.data() + (size_t)r * W;
-            uint32_t *len = h_out + w++;
-            uint32_t n = 0;
-            for (int q = 0; q < W; ++q)
-                for (uint32_t v = K[q]; v; v &= v - 1) {
-                    h_out[w++] = sf.mask[q * 32 + __builtin_ctz(v)];
-                    ++n;
-                }
-            *len = n;
+    auto plan = [&]() -> int {  // after the histograms, on one thread
+        if (bad) return WPM_EINVAL;
+        int64_t total_n = 0, fw = 0, kw = 0, sw = 0;
+        for (int i = 0; i < num; ++i) {
+            int64_t c = 0;
+            for (int64_t r = 0; r < ranges; ++r) {
+                int64_t &h = hist[(size_t)r * num + i];
+                const int64_t v = h;
+                h = total_n + c;  // this range's first position for instance i
+                c += v;
+            }
+            if ((uint64_t)c != h_counts[i]) return WPM_EINVAL;
+            Collected &ci = cs[i];
+            ci.W = (insts[i].M + 31) / 32;
+            ci.first = total_n;
+            ci.n = c;
+            total_n += c;
+            if (!c) continue;
+            ci.buckets = c > 4 * CHUNK ? (int)std::min<int64_t>(256, c / CHUNK) : 1;
+            ci.chunks = (c + CHUNK - 1) / CHUNK;
+            ci.chunk0 = (int64_t)chunk_tasks.size();
+            ci.bucket0 = (int64_t)bucket_tasks.size();
+            for (int64_t q = 0; q < ci.chunks; ++q) chunk_tasks.push_back({i, (int32_t)q});
+            for (int q = 0; q < ci.buckets; ++q) bucket_tasks.push_back({i, q});
+            fw += insts[i].M + (int64_t)insts[i].k * ci.W + ci.W;
+            kw += c * ci.W;
+            sw += ci.buckets - 1;
         }
-        std::vector<uint32_t>().swap(kv);
-    }, 1);
-    return WPM_OK;
+        facet_words.assign((size_t)fw, 0u);
+        splits.assign((size_t)sw, Key{0, 0});
+        if (!xs.reset((size_t)total_n) || !keys.reset((size_t)total_n) || !kv.reset((size_t)kw) ||
+            !bucket_of.reset((size_t)total_n) || (write && !refs.reset((size_t)total_n)))
+            return WPM_ELIMIT;
+        cell0.resize(chunk_tasks.size());
+        int64_t nc = 0;
+        for (size_t t = 0; t < chunk_tasks.size(); ++t) {
+            cell0[t] = nc;
+            nc += cs[chunk_tasks[t].inst].buckets;
+        }
+        cells.assign((size_t)nc, Cell{0, 0});
+        starts.assign(bucket_tasks.size(), Cell{0, 0});
+        uint32_t *f = facet_words.data(), *v = kv.get();
+        Key *sp = splits.data();
+        for (int i = 0; i < num; ++i) {
+            Collected &ci = cs[i];
+            if (!ci.n) continue;
+            ci.mask = f;
+            ci.basis = ci.mask + insts[i].M;
+            ci.off = ci.basis + (size_t)insts[i].k * ci.W;
+            f = ci.off + ci.W;
+            ci.kv = v;
+            v += ci.n * ci.W;
+            ci.split = sp;
+            sp += ci.buckets - 1;
+        }
+        return WPM_OK;
+    };
+    Team team;
+    auto work = [&](int t) {
+        team.share(0, ranges, 1, [&](int64_t r) {
+            int64_t *h = hist.data() + (size_t)r * num;
+            const uint64_t e = std::min<uint64_t>(slots, (uint64_t)(r + 1) * per);
+            for (uint64_t q = (uint64_t)r * per; q < e; ++q) {
+                const uint64_t inst = rec[2 * q + 1];
+                if (inst == ~0ull) continue;
+                if (inst >= (uint64_t)num) { bad = 1; return; }
+                const uint64_t x = rec[2 * q];
+                if (insts[inst].k < 64 && (x >> insts[inst].k)) { bad = 1; return; }
+                ++h[inst];
+            }
+        });
+        team.barrier();
+        if (t == 0) {
+            try {
+                rc = plan();
+            } catch (const std::bad_alloc &) {
+                rc = WPM_ELIMIT;
+            }
+            stop = rc != WPM_OK;
+        }
+        team.barrier();
+        if (stop) return;
+        team.share(1, ranges, 1, [&](int64_t r) {
+            int64_t *h = hist.data() + (size_t)r * num;
+            const uint64_t e = std::min<uint64_t>(slots, (uint64_t)(r + 1) * per);
+            for (uint64_t q = (uint64_t)r * per; q < e; ++q) {
+                const uint64_t inst = rec[2 * q + 1];
+                if (inst != ~0ull) xs[(size_t)h[inst]++] = rec[2 * q];
+            }
+        });
+        team.barrier();
+        // facets, and key ranges by a sample of the instance's results
+        team.share(2, num, 4, [&](int64_t i) {
+            Collected &c = cs[(size_t)i];
+            if (!c.n) return;
+            sort_facets(insts[i], c);
+            if (c.buckets == 1) return;
+            Key sample[1024];
+            uint32_t K[WPM_MAX_M / 32];
+            const int m = std::min(1024, c.buckets * 16);
+            for (int q = 0; q < m; ++q) {
+                expand(c, xs[(size_t)(c.first + c.n * q / m)], K);
+                sample[q] = order_key(K, c.W);
+            }
+            std::sort(sample, sample + m);
+            for (int q = 1; q < c.buckets; ++q) c.split[q - 1] = sample[(int64_t)m * q / c.buckets];
+        });
+        team.barrier();
+        team.share(3, (int64_t)chunk_tasks.size(), 2, [&](int64_t ct) {
+            const Task tk = chunk_tasks[(size_t)ct];
+            const Collected &c = cs[(size_t)tk.inst];
+            Cell *cell = cells.data() + cell0[(size_t)ct];
+            const int64_t r1 = std::min<int64_t>(c.n, (tk.sub + 1) * CHUNK);
+            for (int64_t r = tk.sub * CHUNK; r < r1; ++r) {
+                uint32_t *K = c.kv + (size_t)r * c.W;
+                expand(c, xs[(size_t)(c.first + r)], K);
+                const Key key = order_key(K, c.W);
+                const int b = c.buckets == 1 ? 0 : (int)(std::upper_bound(c.split, c.split + c.buckets - 1, key) - c.split);
+                keys[(size_t)(c.first + r)] = key;
+                bucket_of[(size_t)(c.first + r)] = (uint8_t)b;
+                ++cell[b].n;
+                int64_t w = 1;
+                for (int q = 0; q < c.W; ++q) w += __builtin_popcount(K[q]);
+                cell[b].words += w;
+            }
+        });
+        team.barrier();
+        // places: per instance, bucket by bucket, chunk by chunk
+        team.share(4, num, 16, [&](int64_t i) {
+            Collected &c = cs[(size_t)i];
+            int64_t n = 0, w = 0;
+            for (int b = 0; c.n && b < c.buckets; ++b) {
+                starts[(size_t)(c.bucket0 + b)] = {n, w};
+                for (int64_t q = 0; q < c.chunks; ++q) {
+                    Cell &cell = cells[(size_t)(cell0[(size_t)(c.chunk0 + q)] + b)];
+                    const int64_t m = cell.n;
+                    cell.n = n;
+                    n += m;
+                    w += cell.words;
+                }
+            }
+            c.words = w;
+        });
+        team.barrier();
+        if (t == 0) {
+            int64_t words = 0;
+            for (int i = 0; i < num; ++i) {
+                h_offsets[i] = words;
+                words += cs[(size_t)i].words;
+            }
+            h_offsets[num] = words;
+            *out_words = words;
+            if (!write || out_cap < words) rc = WPM_ECAP;
+            stop = rc != WPM_OK;
+        }
+        team.barrier();
+        if (stop) return;
+        team.share(5, (int64_t)chunk_tasks.size(), 4, [&](int64_t ct) {
+            const Task tk = chunk_tasks[(size_t)ct];
+            const Collected &c = cs[(size_t)tk.inst];
+            Cell *cell = cells.data() + cell0[(size_t)ct];
+            const int64_t r1 = std::min<int64_t>(c.n, (tk.sub + 1) * CHUNK);
+            for (int64_t r = tk.sub * CHUNK; r < r1; ++r) {
+                const size_t at = (size_t)(c.first + r);
+                refs[(size_t)(c.first + cell[bucket_of[at]].n++)] = {keys[at], r};
+            }
+        });
+        team.barrier();
+        // each bucket: canonical order, then the facet lists
+        team.share(6, (int64_t)bucket_tasks.size(), 1, [&](int64_t bt) {
+            const Task tk = bucket_tasks[(size_t)bt];
+            const Collected &c = cs[(size_t)tk.inst];
+            const int W = c.W;
+            Ref *r0 = refs.get() + c.first + starts[(size_t)bt].n;
+            Ref *r1 = refs.get() + c.first + (tk.sub + 1 < c.buckets ? starts[(size_t)bt + 1].n : c.n);
+            std::sort(r0, r1, [&](const Ref &a, const Ref &b) {
+                if (!(a.key == b.key)) return a.key < b.key;
+                return canon_less(c.kv + (size_t)a.idx * W, c.kv + (size_t)b.idx * W, W);
+            });
+            uint32_t *out = h_out + h_offsets[tk.inst] + starts[(size_t)bt].words;
+            for (const Ref *r = r0; r < r1; ++r) {
+                const uint32_t *K = c.kv + (size_t)r->idx * W;
+                uint32_t *len = out++;
+                for (int q = 0; q < W; ++q)
+                    for (uint32_t v = K[q]; v; v &= v - 1) *out++ = c.mask[q * 32 + __builtin_ctz(v)];
+                *len = (uint32_t)(out - len - 1);
+            }
+        });
+    };
+    team.run(want, work);
+    return rc;
 }
 
 }  // namespace wpm

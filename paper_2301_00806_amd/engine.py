@@ -399,6 +399,28 @@ class DeviceBatch:
             self._cq = out
         return self._cq
 
+    def host_views(self):
+        """(wpm_host_instance array, words a result of each instance takes at
+        most), built once per batch: the views point into the instances'
+        own arrays, which the array keeps alive."""
+        if getattr(self, "_views", None) is None:
+            hosts = (L.HostInstance * max(1, len(self.preps)))()
+            keep = []
+            for i, p in enumerate(self.preps):
+                Bf = np.ascontiguousarray(p.basis.reshape(-1), dtype=np.uint32)
+                if Bf.size == 0:
+                    Bf = np.zeros(1, np.uint32)
+                off = None if p.offset is None else np.ascontiguousarray(p.offset, dtype=np.uint32)
+                keep.append((p.facets, Bf, off))
+                hosts[i] = L.HostInstance(M=len(p.facets), k=p.k, facets=p.facets.ctypes.data,
+                                          basis=Bf.ctypes.data,
+                                          offset=None if off is None else off.ctypes.data)
+            per = np.array([1 + (min(len(p.facets), p.max_facets) if p.max_facets > 0 else len(p.facets))
+                            for p in self.preps], dtype=np.int64)
+            hosts.keep = keep  # as long as any caller holds the array
+            self._views = (hosts, per)
+        return self._views
+
     def class_grid(self, cls: int, wg_size: int) -> int:
         """persistent_grid of one launch class, cached per workgroup size."""
         if getattr(self, "_grids", None) is None:
@@ -821,20 +843,7 @@ class Sweeper:
         if stream is None:
             stream = torch.cuda.current_stream()
         preps = self.batch.preps
-        hosts = (L.HostInstance * max(1, len(preps)))()
-        keep = []
-        for i, p in enumerate(preps):
-            Bf = np.ascontiguousarray(p.basis.reshape(-1), dtype=np.uint32)
-            if Bf.size == 0:
-                Bf = np.zeros(1, np.uint32)
-            keep.append(Bf)
-            off = None
-            if p.offset is not None:
-                off = np.ascontiguousarray(p.offset, dtype=np.uint32)
-                keep.append(off)
-            hosts[i] = L.HostInstance(M=len(p.facets), k=p.k, facets=p.facets.ctypes.data,
-                                      basis=Bf.ctypes.data,
-                                      offset=None if off is None else off.ctypes.data)
+        hosts, per = self.batch.host_views()
         h_counts = np.zeros(max(1, len(preps)), dtype=np.uint64)
         offs = np.zeros(len(preps) + 1, dtype=np.int64)
         words = ctypes.c_int64(0)
@@ -854,8 +863,6 @@ class Sweeper:
         # One call with an output sized by the bound 1 + min(M, facet bound)
         # words per result; pages past the words written are never touched.
         cnt = self.counts[:len(preps)].cpu().numpy().astype(np.int64) if len(preps) else np.zeros(0, np.int64)
-        per = np.array([1 + (min(len(p.facets), p.max_facets) if p.max_facets > 0 else len(p.facets))
-                        for p in preps], dtype=np.int64)
         bound = int((cnt * per).sum()) if len(preps) else 0
         out = np.empty(max(1, bound), dtype=np.uint32)
         st = lib.wpm_collect(*args, _ptr(out), bound, ctypes.byref(words),

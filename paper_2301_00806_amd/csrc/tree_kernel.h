@@ -665,19 +665,25 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
 #pragma unroll
                         for (int b = 0; b < WIN_BITS / 3; ++b)
                             o[b] = (8u * b + ((gr >> (3 * b)) & 7u)) * (uint32_t)S;
+                        // All eight loads of a word are in flight: a check is a chain of
+                        // LDS round trips, and three loads at a time made it
+                        // three times as long (three facet sets, k = 32..36: 609
+                        // -> 554 us a sweep; 1024 maps 1.32 -> 1.27 ms).
                         auto word4 = [&](int off) {
+                            asm volatile("" : "+s"(off));  // (one set of addresses, not one per slot group)
+                            uint4 p[WIN_BITS / 3];
                             uint4 r = *(const uint4 *)(lds_win + off);
 #pragma unroll
+                            for (int b = 0; b < WIN_BITS / 3; ++b) p[b] = *(const uint4 *)(lds_X + o[b] + off);
+                            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
                             for (int b = 0; b < WIN_BITS / 3; b += 2) {
-                                const uint4 p = *(const uint4 *)(lds_X + o[b] + off);
                                 uint4 q = {0u, 0u, 0u, 0u};
-                                if (b + 1 < WIN_BITS / 3) q = *(const uint4 *)(lds_X + o[b + 1] + off);
-                                r.x = xor3(r.x, p.x, q.x);
-                                r.y = xor3(r.y, p.y, q.y);
-                                r.z = xor3(r.z, p.z, q.z);
-                                r.w = xor3(r.w, p.w, q.w);
-                                // (four loads in flight, within the register budget)
-                                if (b == 2) asm volatile("" : "+v"(r.x), "+v"(r.y), "+v"(r.z), "+v"(r.w)::"memory");
+                                if (b + 1 < WIN_BITS / 3) q = p[b + 1];
+                                r.x = xor3(r.x, p[b].x, q.x);
+                                r.y = xor3(r.y, p[b].y, q.y);
+                                r.z = xor3(r.z, p[b].z, q.z);
+                                r.w = xor3(r.w, p[b].w, q.w);
                             }
                             return r;
                         };

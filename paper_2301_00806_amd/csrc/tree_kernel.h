@@ -35,9 +35,10 @@
 // split and spread over the workgroups by the host.
 //
 // Measured against the walk of every vector (ms a sweep, same outputs): 1024
-// maps of n = 5..8, k <= 34, 7.4e10 vectors 9.00 -> 1.19; 512 of n = 4..7 1.59 ->
-// 0.47; three facet sets of 7-subsets of [11], k = 32..36, 11.7 -> 0.60; a slice
-// of 1.5e10 pruned vectors of an n = 9 orbit 1.74 -> 0.19.
+// maps of n = 5..8, k <= 34, 7.4e10 vectors 8.1 -> 1.1; 512 of n = 4..7 1.72 ->
+// 0.44; three facet sets of 7-subsets of [11], k = 32..36, 10.5 -> 0.62; a slice
+// of 1.5e10 pruned vectors of an n = 9 orbit 1.77 -> 0.19.  16384 maps of n = 5..8,
+// k <= 36, 1.04e12 vectors: 114 -> 7.4.
 #pragma once
 
 #include "sweep_kernel.h"
@@ -111,6 +112,7 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
         uint64_t taken, results;
         uint64_t item, since;  // of the last claim
         uint32_t claim;
+        __attribute__((aligned(16))) wpm_item items[MAX_CLAIM + 1];  // of the last claim
         uint64_t dense[3];  // dense groups of a block of 64, by turns
         __attribute__((aligned(16))) uint32_t head[16];  // the staged table's header
     };
@@ -213,6 +215,13 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
                     sh.claim = n;
                     sh.item = add64(a.head, n) + (uint64_t)gridDim.x;
                 }
+                if (wv == 0) {
+                    // the claim's items at once (loaded one by one, two loads were
+                    // on each item's path: 512 maps 428 -> 419 us a sweep, 1024
+                    // maps 1122 -> 1104, three facet sets of k = 32..36 670 -> 635)
+                    const int64_t i = (int64_t)(rfl64(sh.item) >> split) + lane_now();
+                    if (lane_now() <= MAX_CLAIM && i < vnum >> split) sh.items[lane_now()] = items[i];
+                }
                 __syncthreads();
                 vt = (int64_t)rfl64(sh.item);
                 vend = vt + (int64_t)__builtin_amdgcn_readfirstlane(sh.claim);
@@ -224,12 +233,14 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
         }
         if (vt >= vnum) break;
         if (vend > vnum) vend = vnum;
+        const int64_t held = mode == 2 && round > 0 ? vt >> split : INT64_MAX;
+        auto item_at = [&](int64_t i) -> wpm_item { return i >= held ? sh.items[i - held] : items[i]; };
         for (; vt < vend; ++vt) {
             const int64_t it = vt >> split;
             const uint32_t part = (uint32_t)vt & ((1u << split) - 1u);
             uint64_t t_start = 0;
             if (timed) t_start = __builtin_amdgcn_s_memrealtime();
-            const wpm_item itm = items[it];
+            const wpm_item itm = item_at(it);
             const uint32_t inst = __builtin_amdgcn_readfirstlane(itm.instance);
             const int c = (int)__builtin_amdgcn_readfirstlane((uint32_t)itm.cbits);
             const int lanes = (int)__builtin_amdgcn_readfirstlane((uint32_t)itm.lanes);
@@ -343,7 +354,7 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
             // the list is emptied when the instance or the claim ends
             bool last = true;
             while (!timed && vt + 1 < vend) {
-                const wpm_item nx = items[(vt + 1) >> split];
+                const wpm_item nx = item_at((vt + 1) >> split);
                 const int nc = (int)__builtin_amdgcn_readfirstlane((uint32_t)nx.cbits);
                 const int nl = (int)__builtin_amdgcn_readfirstlane((uint32_t)nx.lanes);
                 const uint64_t nf = rfl64(nx.first);

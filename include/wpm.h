@@ -434,12 +434,15 @@ typedef struct wpm_sched {
     const wpm_item *d_items;   /* device: the items */
     const wpm_item *h_items;   /* host copy (PLAIN mode launches per instance from it) */
     int64_t num_items;
-    uint32_t *d_scratch;       /* device: >= 4 words (queue head), cleared by the call */
+    uint32_t *d_scratch;       /* device: >= 4 words (queue heads), cleared by the call */
     uint64_t *d_item_times;    /* optional device [num_items][2]: start, end (s_memrealtime) */
     const int64_t *d_bin_offsets; /* PACKED mode: device [grid + 1] from wpm_pack_bins */
     int32_t waves_per_simd;    /* register budget of the kernel: 7 or 8 waves per SIMD (0 = 8) */
-    int32_t reserved;
+    int32_t scratch_words;     /* words at d_scratch (0 = 4).  With WPM_QUEUE_SCRATCH_WORDS the
+                                * dynamic queue has eight heads instead of one */
 } wpm_sched;
+
+#define WPM_QUEUE_SCRATCH_WORDS 288
 
 /* Workgroups a persistent launch of this batch uses by default: the
  * occupancy of the selected kernel instantiation times the compute units. */

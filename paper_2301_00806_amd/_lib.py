@@ -13,6 +13,7 @@ FLAG_ACCUMULATE = 1
 BATCH_TREE, BATCH_WALK = 1, 2
 CX_FULL_PICARD, CX_SEED = 1, 2
 TOTAL_WORDS = 4
+QUEUE_SCRATCH_WORDS = 288
 MAX_ROW_WORDS = 160
 LANE_WINDOW = 512
 MAX_K = 64
@@ -66,7 +67,7 @@ class Sched(ctypes.Structure):
                 ("h_items", ctypes.c_void_p), ("num_items", ctypes.c_int64),
                 ("d_scratch", ctypes.c_void_p), ("d_item_times", ctypes.c_void_p),
                 ("d_bin_offsets", ctypes.c_void_p), ("waves_per_simd", ctypes.c_int32),
-                ("reserved", ctypes.c_int32)]
+                ("scratch_words", ctypes.c_int32)]
 
 
 class HostInstance(ctypes.Structure):

@@ -95,6 +95,7 @@ struct KArgs {
     int count_bad;       // malformed items are counted by this launch
     int alone;           // no launch of the other kernel: its items are malformed
     int split;           // descent: every item is handed out as 2^split parts
+    int queues;          // descent: queue heads (a power of two, 16 words apart)
 };
 
 // Per ridge bit: at least 3 of the slot bits (a, b, c, d) set, given the

@@ -37,7 +37,7 @@
 // Measured against the walk of every vector (ms a sweep, same outputs): 1024
 // maps of n = 5..8, k <= 34, 7.4e10 vectors 8.1 -> 1.1; 512 of n = 4..7 1.72 ->
 // 0.44; three facet sets of 7-subsets of [11], k = 32..36, 10.5 -> 0.62; a slice
-// of 1.5e10 pruned vectors of an n = 9 orbit 1.77 -> 0.19.  16384 maps of n = 5..8,
+// of 1.5e10 pruned vectors of an n = 9 orbit 1.77 -> 0.11.  16384 maps of n = 5..8,
 // k <= 36, 1.04e12 vectors: 114 -> 7.4.
 #pragma once
 
@@ -59,6 +59,8 @@ constexpr int CHILD_LIST = 128;                 // children a wave's list holds
 constexpr int TREE_MIN_SPLIT = 1 << 16;         // vectors a part of a split item keeps at least
 constexpr uint32_t CLAIM_TIME = 5000;           // of a claim, in 10 ns
 constexpr int MAX_CLAIM = 16;                   // items of a claim, at most
+constexpr int HEAD_STRIDE = 16;                 // words from queue head to queue head (128 bytes)
+constexpr int QUEUE_BLOCK = 64;                 // (parts of) items a queue holds in a row
 constexpr int DENSE_GROUP = 16;                 // surviving nodes that make a group dense
 
 // Row stride of the window tables: an odd number of 16-byte units, so that the
@@ -91,6 +93,9 @@ typedef __attribute__((address_space(1))) unsigned long long gu64;
 __device__ __forceinline__ uint64_t add64(unsigned long long *p, uint64_t v) {
     return __hip_atomic_fetch_add((gu64 *)p, (unsigned long long)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+__device__ __forceinline__ uint64_t look64(const unsigned long long *p) {
+    return __hip_atomic_load((const gu64 *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 __device__ __forceinline__ void put64(uint64_t *p, uint64_t v) { *(gu64 *)p = v; }
 
 template <int WAVES>
@@ -111,7 +116,7 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
         uint64_t block;    // of record slots: base << 28 | log2 size << 24 | used (size 0: none yet)
         uint64_t taken, results;
         uint64_t item, since;  // of the last claim
-        uint32_t claim;
+        uint32_t claim, ticket, queue;
         __attribute__((aligned(16))) wpm_item items[MAX_CLAIM + 1];  // of the last claim
         uint64_t dense[3];  // dense groups of a block of 64, by turns
         __attribute__((aligned(16))) uint32_t head[16];  // the staged table's header
@@ -182,7 +187,8 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
         // ---- the (parts of) items this workgroup takes next.  In the
         // dynamic mode the first is fixed, the others come from the queue's
         // counter.
-        int64_t vt, vend;
+        int64_t vt, vend, vnext = 0;
+        uint32_t rest = 0;
         if (mode == 0) {
             if (round > 0) break;
             vt = (int64_t)rfl64((uint64_t)a.item_base) + (int64_t)blockIdx.x;
@@ -198,22 +204,58 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
             if (round == 0) {
                 vt = (int64_t)blockIdx.x;
                 vend = vt + 1;
-                if (tid_now() == 0) sh.claim = 1;
+                if (tid_now() == 0) {
+                    sh.claim = 1;
+                    sh.queue = blockIdx.x & (uint32_t)(a.queues - 1);
+                }
             } else {
                 if ((int64_t)gridDim.x >= vnum) break;
-                if (tid_now() == 0) {
+                if (wv == 0) {
                     // so many items that they take CLAIM_TIME at the last
                     // claim's pace (their density is that of their
                     // neighbours in the queue), and no more than a share of
                     // what is left
                     const uint64_t now = __builtin_amdgcn_s_memrealtime();
-                    const uint32_t n0 = sh.claim, pace = (uint32_t)(now - sh.since) / n0 + 1u;
-                    const int64_t left = (vnum - (int64_t)sh.item) / (16 * (int64_t)gridDim.x);
+                    const uint32_t n0 = __builtin_amdgcn_readfirstlane(sh.claim),
+                                   pace = (uint32_t)(now - rfl64(sh.since)) / n0 + 1u;
+                    const int64_t left = (vnum - (int64_t)rfl64(sh.item)) / (16 * (int64_t)gridDim.x);
                     uint32_t n = CLAIM_TIME / pace;
                     if ((int64_t)n > left) n = (uint32_t)left;
                     n = timed || n < 1u ? 1u : n > (uint32_t)MAX_CLAIM ? (uint32_t)MAX_CLAIM : n;
-                    sh.claim = n;
-                    sh.item = add64(a.head, n) + (uint64_t)gridDim.x;
+                    // The items go round the queues in blocks; ticket t of queue
+                    // q is (part of) item v, v rising with t.  An empty queue is
+                    // left for another.  One head hands out a claim in 12 ns:
+                    // where items are cheap, so that claims are short, 14,641
+                    // of them were 190 us and are 105 from eight heads (1024
+                    // maps 940 -> 875 us a sweep, 512 maps 431 -> 406, three
+                    // facet sets of k = 32..36 557 -> 494).
+                    uint32_t q = __builtin_amdgcn_readfirstlane(sh.queue);
+                    const uint32_t nq = __builtin_amdgcn_readfirstlane((uint32_t)a.queues);
+                    auto place = [&](uint64_t t, uint32_t of) -> int64_t {
+                        return (int64_t)gridDim.x +
+                               (int64_t)((t / QUEUE_BLOCK * nq + of) * QUEUE_BLOCK + t % QUEUE_BLOCK);
+                    };
+                    int64_t v;
+                    uint64_t t;
+                    for (;;) {
+                        t = 0;
+                        if (lane_now() == 0) t = add64(a.head + HEAD_STRIDE * q, n);
+                        t = rfl64(t);
+                        v = place(t, q);
+                        if (v < vnum) break;
+                        const uint32_t ln = (uint32_t)lane_now();
+                        const bool some = ln < nq && place(look64(a.head + HEAD_STRIDE * (ln < nq ? ln : 0u)), ln) < vnum;
+                        const uint32_t m = (uint32_t)__builtin_amdgcn_ballot_w64(some);
+                        if (m == 0) break;
+                        const uint32_t after = m & (0u - (2u << q));  // the next such queue, round from q
+                        q = (uint32_t)__builtin_ctz(after ? after : m);
+                    }
+                    if (lane_now() == 0) {
+                        sh.claim = n;
+                        sh.ticket = (uint32_t)(t % QUEUE_BLOCK);
+                        sh.queue = q;
+                        sh.item = (uint64_t)v;
+                    }
                 }
                 if (wv == 0) {
                     // the claim's items at once (loaded one by one, two loads were
@@ -224,7 +266,13 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
                 }
                 __syncthreads();
                 vt = (int64_t)rfl64(sh.item);
-                vend = vt + (int64_t)__builtin_amdgcn_readfirstlane(sh.claim);
+                const uint32_t n = __builtin_amdgcn_readfirstlane(sh.claim),
+                               room = (uint32_t)QUEUE_BLOCK - __builtin_amdgcn_readfirstlane(sh.ticket);
+                vend = vt + (int64_t)(n < room ? n : room);
+                if (n > room) {  // it goes on in the queue's next block
+                    rest = n - room;
+                    vnext = vend + (int64_t)(__builtin_amdgcn_readfirstlane((uint32_t)a.queues) - 1) * QUEUE_BLOCK;
+                }
             }
             if (tid_now() == 0) {
                 sh.since = __builtin_amdgcn_s_memrealtime();
@@ -233,9 +281,15 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
         }
         if (vt >= vnum) break;
         if (vend > vnum) vend = vnum;
-        const int64_t held = mode == 2 && round > 0 ? vt >> split : INT64_MAX;
-        auto item_at = [&](int64_t i) -> wpm_item { return i >= held ? sh.items[i - held] : items[i]; };
-        for (; vt < vend; ++vt) {
+        const int64_t held = mode == 2 && round > 0 ? vt >> split : INT64_MAX - MAX_CLAIM;
+        auto item_at = [&](int64_t i) -> wpm_item { return i >= held && i <= held + MAX_CLAIM ? sh.items[i - held] : items[i]; };
+        for (;; ++vt) {
+            if (vt >= vend) {
+                if (rest == 0 || vnext >= vnum) break;
+                vt = vnext;
+                vend = vnext + rest < vnum ? vnext + (int64_t)rest : vnum;
+                rest = 0;
+            }
             const int64_t it = vt >> split;
             const uint32_t part = (uint32_t)vt & ((1u << split) - 1u);
             uint64_t t_start = 0;

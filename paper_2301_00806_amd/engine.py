@@ -603,9 +603,10 @@ class Sweeper:
         # [results, record slots, malformed items skipped, 0]
         self.total = torch.empty(L.TOTAL_WORDS, dtype=torch.int64, device=device)
         self.stats = torch.empty(8, dtype=torch.int64, device=device)
-        self.scratch = torch.empty(4, dtype=torch.int64, device=device)
+        self.scratch = torch.empty(L.QUEUE_SCRATCH_WORDS // 2, dtype=torch.int64, device=device)
         self._items_dev = None
         self._items_host = None
+        self._items_ptr = 0
         self._times = None
         self._segments = []
         self._seg_bins = []
@@ -628,6 +629,7 @@ class Sweeper:
         if pinned is not None and (items.ctypes.data != pinned.data_ptr() or not items.flags["C_CONTIGUOUS"]):
             pinned = None   # a view into the pinned array: copied the plain way
         self._items_host = items if pinned is not None else np.ascontiguousarray(items)
+        self._items_ptr = self._items_host.ctypes.data if len(items) else 0
         self._segments = segments
         self._seg_bins = [None if sg.bins is None else torch.from_numpy(
             np.ascontiguousarray(sg.bins, np.int64)).to(self.device) for sg in segments]
@@ -652,7 +654,6 @@ class Sweeper:
         torch = self.torch
         if stream is None:
             stream = torch.cuda.current_stream()
-        items = self._items_host
         segs = self._segments or [Segment(None, 0, 0)]
         self.seg_events = []
         for i, sg in enumerate(segs):
@@ -666,11 +667,11 @@ class Sweeper:
             s = L.Sched(mode=mode, wg_size=wg_size, grid=grid,
                         flags=L.FLAG_ACCUMULATE if (i or accumulate) else 0,
                         d_items=self._items_dev.data_ptr() + 16 * sg.start,
-                        h_items=items.ctypes.data + 16 * sg.start if n else None,
+                        h_items=self._items_ptr + 16 * sg.start if n else None,
                         num_items=n, d_scratch=self.scratch.data_ptr(),
                         d_item_times=(self._times.data_ptr() + 16 * sg.start) if self._times is not None else None,
                         d_bin_offsets=bins.data_ptr() if bins is not None else None,
-                        waves_per_simd=waves)
+                        waves_per_simd=waves, scratch_words=L.QUEUE_SCRATCH_WORDS)
             if mode == L.SCHED_PACKED:
                 if bins is None:
                     raise ValueError("packed mode needs per-segment bins")
@@ -743,7 +744,8 @@ class Sweeper:
                         h_items=items.ctypes.data + 16 * a0 if n else None,
                         num_items=n, d_scratch=self.scratch.data_ptr(),
                         d_item_times=(self._times.data_ptr() + 16 * a0) if self._times is not None else None,
-                        d_bin_offsets=None, waves_per_simd=waves)
+                        d_bin_offsets=None, waves_per_simd=waves,
+                        scratch_words=L.QUEUE_SCRATCH_WORDS)
             if mode == L.SCHED_PACKED:  # never split: the bins cover the whole segment
                 bins = self._seg_bins[i] if self._segments else None
                 if bins is None:

@@ -39,6 +39,33 @@ INT32_PEAK = 256 * 128 * 2.4e9
 # Fast filter per kernel vector: 4 XORs and 2 threshold ops, plus a 3-input
 # minimum, a minimum and a compare shared by the four chains of a step.
 ALG_OPS_PER_VECTOR = 4 + 2 + 3 / 4
+# Tree descent, int32 ops for each of the 64 parts of an opened sub-cube: of
+# 2^18 vectors (4 XORs, 2 threshold ops), of 2^12 (two ridge groups: 8 XORs, 4
+# threshold ops, 1 OR), of 2^6 (4 XORs, 2 threshold ops, a compare and an add
+# that collects its bit).  The checks of candidates are not counted.
+DESCENT_OPS = (6, 13, 8)
+
+
+def walked(p) -> bool:
+    """Is this instance's table without a level section (swept vector by
+    vector)?"""
+    return not int(p.table[11]) & 2
+
+
+def sweep_ops(preps, stats) -> float:
+    """int32 ops of the tests a sweep of `preps` made: the descent's by the
+    sub-cubes it opened, the walk's by vectors."""
+    ops = 64.0 * sum(c * float(n) for c, n in zip(DESCENT_OPS, stats[5:8]))
+    return ops + ALG_OPS_PER_VECTOR * float(sum(int(p.visited) for p in preps if p.k > 0 and walked(p)))
+
+
+def kernel_sources_sha256() -> str:
+    import hashlib
+    h = hashlib.sha256()
+    for f in ("sweep_kernel.h", "tree_kernel.h"):
+        with open(os.path.join(ROOT, "paper_2301_00806_amd", "csrc", f), "rb") as src:
+            h.update(src.read())
+    return h.hexdigest()
 
 
 def ops_alg_plain(p) -> int:
@@ -319,6 +346,7 @@ def main():
     torch.cuda.synchronize()
     seg_ms = {(None if cls is None else int(cls)): a0.elapsed_time(a1) for cls, a0, a1 in sw.seg_events}
     assert np.array_equal(sw.counts[:len(preps)].cpu().numpy().astype(np.uint64), res_b.counts)
+    roof_stats = sw.stats.cpu().numpy().astype(np.uint64)
 
     # ---- end to end once: packed tables host -> HBM, one step, records back
     # and expanded into canonical facet lists by wpm_collect
@@ -369,7 +397,9 @@ def main():
     dom = max(cls_vec, key=cls_vec.get)
     dom_ms = seg_ms[dom]
     waves_used = args.waves if args.waves in (7, 8) else 8
-    dom_name = "sweep_kernel<%d> (rows of at most %d words)" % (waves_used, dom)
+    dom_preps = [p for p, c in zip(preps, batch.cls) if int(c) == dom and p.k > 0]
+    kinds = {"sweep_kernel<%d>" % waves_used if walked(p) else "tree_kernel<7>" for p in dom_preps}
+    dom_name = "%s (rows of at most %d words)" % (" + ".join(sorted(kinds)), dom)
     log(f"dominant launch {dom_name}: {cls_vec[dom]:.4e} vectors in {dom_ms:.2f} ms "
         f"({cls_vec[dom] / dom_ms * 1e3:.3e} vectors/s); per-class ms {seg_ms}")
     out = {}
@@ -430,8 +460,8 @@ def main():
                   "ms_per_step": t_p * 1e3, "kernel_ms": k_p,
                   "covered_per_s": vectors / t_p, "visited_per_s": visited / t_p,
                   "speedup_vs_learned_step": t_b / t_p, "prep_s": prep_s,
-                  # the fast filter's ops per visited vector over the kernel time
-                  "frac_per_visited": ALG_OPS_PER_VECTOR * visited / (k_p * 1e-3) / INT32_PEAK,
+                  # the tests' ops over the kernel time
+                  "frac_of_peak": sweep_ops(preps_p, res_p.stats) / (k_p * 1e-3) / INT32_PEAK,
                   "counts_equal_to_full_sweep": True}
         del sw_p, batch_p
 
@@ -465,7 +495,10 @@ def main():
             b.copy_(a)
         torch.cuda.synchronize()
 
-    achieved = ALG_OPS_PER_VECTOR * cls_vec[dom] / (dom_ms * 1e-3) / 1e12
+    # (the statistics are of all classes, whose other members hold a negligible
+    # share of the work)
+    dom_ops = sweep_ops(preps, roof_stats)
+    achieved = dom_ops / (dom_ms * 1e-3) / 1e12
     # the same launch priced at the plain per-ridge check's work per vector
     # (AND + popcount per parent word of every critical ridge), weighted by 2^k
     plain_ops = sum(float(1 << p.k) * ops_alg_plain(p) for p, c in zip(preps, batch.cls)
@@ -473,32 +506,23 @@ def main():
     plain_per_vec = plain_ops / cls_vec[dom]
     effective = plain_ops / (dom_ms * 1e-3) / 1e12
     probe = E.valu_probe(0, 4)
-    # the fast step's instruction-mix ceiling: per vector 4.5 two-source ops
+    # the walk's fast step: its instruction-mix ceiling: per vector 4.5 two-source ops
     # (4 XORs, a quarter of a minimum and of a compare) and 2.25 three-source
     # ops (2 logic ops, a quarter of a 3-input minimum) at the probe's rates
     probe3 = E.valu_probe(1, 8)
     probe2 = E.valu_probe(0, 8)
     mix_ceiling = ALG_OPS_PER_VECTOR / (4.5 / probe2 + 2.25 / probe3)
-    counters = None
-    cpath = os.path.join(ROOT, "profiles", "sweep_counters.json")
-    if os.path.exists(cpath):
-        import hashlib
-        src = open(os.path.join(ROOT, "paper_2301_00806_amd", "csrc", "sweep_kernel.h"), "rb").read()
-        with open(cpath) as f:
-            cj = json.load(f)
-        if (cj.get("kernel_source_sha256") == hashlib.sha256(src).hexdigest() and cj.get("kernel") == dom_name
-                and cj.get("vectors") == float(cls_vec[dom])):
-            counters = cj
-    traffic = None
-    tpath = os.path.join(ROOT, "profiles", "sweep_traffic.json")
-    if os.path.exists(tpath):
-        import hashlib
-        src = open(os.path.join(ROOT, "paper_2301_00806_amd", "csrc", "sweep_kernel.h"), "rb").read()
-        with open(tpath) as f:
-            tr = json.load(f)
-        if (tr.get("kernel_source_sha256") == hashlib.sha256(src).hexdigest() and tr.get("kernel") == dom_name
-                and tr.get("vectors") == float(cls_vec[dom])):
-            traffic = tr.get("bytes_per_launch")
+    def profiled(name):
+        path = os.path.join(ROOT, "profiles", name)
+        if not os.path.exists(path):
+            return None
+        with open(path) as f:
+            j = json.load(f)
+        same = (j.get("kernel_source_sha256") == kernel_sources_sha256() and j.get("kernel") == dom_name
+                and j.get("vectors") == float(cls_vec[dom]))
+        return j if same else None
+    counters = profiled("sweep_counters.json")
+    traffic = (profiled("sweep_traffic.json") or {}).get("bytes_per_launch")
     line = {
         "metric": "kernel vectors checked/sec + WPM count (bit-exact); batched+learned vs plain",
         "value": vectors / t_b,
@@ -533,12 +557,15 @@ def main():
         "roofline": {"bound": "alu", "achieved": achieved, "peak": INT32_PEAK / 1e12,
                      "unit": "Tops/s (int32 VALU lane-ops)", "frac": achieved / (INT32_PEAK / 1e12),
                      "traffic": traffic, "kernel": dom_name, "kernel_ms": dom_ms,
-                     "vectors_per_launch": cls_vec[dom], "ops_per_vector": ALG_OPS_PER_VECTOR,
+                     "vectors_per_launch": cls_vec[dom], "ops_per_vector": dom_ops / cls_vec[dom],
+                     "subcubes_opened": {b: int(n) for b, n in zip(("2^18", "2^12", "2^6"), roof_stats[5:8])},
+                     "candidates": int(roof_stats[0]),
                      "ops_alg_plain_per_vector": plain_per_vec,
                      "effective_plain": effective, "effective_plain_frac": effective / (INT32_PEAK / 1e12),
-                     "note": "frac prices a vector at the fast filter's 6.75 int32 ops; effective_plain prices it "
-                             "at the plain per-ridge AND+popcount check of the same launch (saved work, "
-                             "not skipped work: every count equals the oracle's)",
+                     "note": "every kernel vector is decided: by a ridge that fails for its whole sub-cube, or "
+                             "down to the vector itself (every count equals the oracle's). frac counts the int32 ops "
+                             "of the tests made; effective_plain prices all vectors at the plain per-ridge "
+                             "AND+popcount check",
                      "measured_int32_xor_peak": probe / 1e12,
                      "mix_ceiling": mix_ceiling / 1e12,
                      "mix_ceiling_frac": mix_ceiling / INT32_PEAK,

@@ -58,6 +58,7 @@ constexpr int TREE_LIST = 192;                  // candidates a wave's list hold
 constexpr int CHILD_LIST = 128;                 // children a wave's list holds
 constexpr int TREE_MIN_SPLIT = 1 << 16;         // vectors a part of a split item keeps at least
 constexpr uint32_t CLAIM_TIME = 5000;           // of a claim, in 10 ns
+constexpr uint32_t LONG_TIME = 1000;            // into a claim a wave's checks go first, in 10 ns
 constexpr int MAX_CLAIM = 16;                   // items of a claim, at most
 constexpr int HEAD_STRIDE = 16;                 // words from queue head to queue head (128 bytes)
 constexpr int QUEUE_BLOCK = 64;                 // (parts of) items a queue holds in a row
@@ -129,6 +130,7 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
     __shared__ Book s_book[512 / 64];
     if (threadIdx.x == 0) {
         s_a = a_in;
+        sh.since = __builtin_amdgcn_s_memrealtime();
         sh.block = sh.taken = sh.results = 0;
         sh.dense[0] = sh.dense[1] = sh.dense[2] = 0;
     }
@@ -265,6 +267,7 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
                     if (lane_now() <= MAX_CLAIM && i < vnum >> split) sh.items[lane_now()] = items[i];
                 }
                 __syncthreads();
+                __builtin_amdgcn_s_setprio(0);
                 vt = (int64_t)rfl64(sh.item);
                 const uint32_t n = __builtin_amdgcn_readfirstlane(sh.claim),
                                room = (uint32_t)QUEUE_BLOCK - __builtin_amdgcn_readfirstlane(sh.ticket);
@@ -692,6 +695,13 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
                 }
                 if (full || (done && last && ccnt == 0u && tcnt != 0u)) {
                     // ---- check: lane j takes entry base + j
+                    // A wave that is long into its claim has dense items, the last
+                    // of the launch to end: it issues before its neighbours
+                    // (512 maps 320 -> 303 us a sweep, 512 pruned 640 -> 600, three
+                    // facet sets of k = 32..36 463 -> 453, 1024 maps 1112 -> 1097;
+                    // 25 and 50 us and other priorities measured the same).
+                    if (mode == 2 && !timed && (uint32_t)(__builtin_amdgcn_s_memrealtime() - rfl64(sh.since)) > LONG_TIME)
+                        __builtin_amdgcn_s_setprio(1);
                     tally(0, tcnt);
                     tally(3, (tcnt + 63) / 64);
                     if (trow != twin) {

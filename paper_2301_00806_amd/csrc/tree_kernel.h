@@ -63,6 +63,10 @@ constexpr int MAX_CLAIM = 16;                   // items of a claim, at most
 constexpr int HEAD_STRIDE = 16;                 // words from queue head to queue head (128 bytes)
 constexpr int QUEUE_BLOCK = 64;                 // (parts of) items a queue holds in a row
 constexpr int DENSE_GROUP = 16;                 // surviving nodes that make a group dense
+// The base of a block of record slots has 44 bits; the top one stands for a
+// block past the caller's records, of which nothing is written.  (Its other
+// bits still differ from one block to the next, which waiting waves look for.)
+constexpr uint64_t PAST_RECORDS = 1ull << 43;
 
 // Row stride of the window tables: an odd number of 16-byte units, so that the
 // 8 rows a wave's lanes pick from start in 8 different bank groups.
@@ -114,7 +118,7 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
     // atomic per check), adds an instance's count once per run of its items and
     // its statistics once.
     struct Shared {
-        uint64_t block;    // of record slots: base << 28 | log2 size << 24 | used (size 0: none yet)
+        uint64_t block;    // of record slots: base << 20 | log2 size << 16 | used (size 0: none yet)
         uint64_t taken, results;
         uint64_t item, since;  // of the last claim
         uint32_t claim, ticket, queue;
@@ -805,18 +809,18 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
                                     const uint64_t old = __hip_atomic_fetch_add(&sh.block, (uint64_t)nbal, __ATOMIC_RELAXED,
                                                                                 __HIP_MEMORY_SCOPE_WORKGROUP);
                                     asm volatile("" ::: "memory");
-                                    const uint32_t used = (uint32_t)old & 0xFFFFFFu, lg = (uint32_t)(old >> 24) & 15u;
+                                    const uint32_t used = (uint32_t)old & 0xFFFFu, lg = (uint32_t)(old >> 16) & 15u;
                                     const uint32_t size = lg ? 1u << lg : 0u;
                                     if (used > size) {  // another wave is getting the next block
                                         // (base and size: the first block's base
                                         // is 0, as before it)
-                                        const uint64_t was = old >> 24;
+                                        const uint64_t was = old >> 16;
                                         while ((__hip_atomic_load(&sh.block, __ATOMIC_RELAXED,
-                                                                  __HIP_MEMORY_SCOPE_WORKGROUP) >> 24) == was)
+                                                                  __HIP_MEMORY_SCOPE_WORKGROUP) >> 16) == was)
                                             __builtin_amdgcn_s_sleep(2);
                                         continue;
                                     }
-                                    pos0 = (old >> 28) + used;
+                                    pos0 = (old >> 20) + used;
                                     room = size - used < nbal ? size - used : nbal;
                                     if (nbal > room) {
                                         const uint32_t over = nbal - room;
@@ -828,7 +832,9 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
                                         __hip_atomic_store(&sh.taken, taken + (1ull << l2), __ATOMIC_RELAXED,
                                                            __HIP_MEMORY_SCOPE_WORKGROUP);
                                         asm volatile("" ::: "memory");
-                                        __hip_atomic_store(&sh.block, next << 28 | (uint64_t)l2 << 24 | over,
+                                        uint64_t base = next & (PAST_RECORDS - 1);
+                                        if (next >= a.cap) base |= PAST_RECORDS;
+                                        __hip_atomic_store(&sh.block, base << 20 | (uint64_t)l2 << 16 | over,
                                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                                     }
                                     break;
@@ -870,9 +876,9 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
     bk.cnt = nres;
     __syncthreads();
     flush_counts();
-    const uint32_t lg = (uint32_t)(sh.block >> 24) & 15u, used = (uint32_t)sh.block & 0xFFFFFFu;
+    const uint32_t lg = (uint32_t)(sh.block >> 16) & 15u, used = (uint32_t)sh.block & 0xFFFFu;
     for (uint32_t e = used + (uint32_t)tid; lg != 0 && e < 1u << lg; e += (uint32_t)bd) {
-        const uint64_t pos = (sh.block >> 28) + e;
+        const uint64_t pos = (sh.block >> 20) + e;
         if (pos < a.cap) {
             put64(a.surv + 2 * pos, 0);
             put64(a.surv + 2 * pos + 1, ~0ull);

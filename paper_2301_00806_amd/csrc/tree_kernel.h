@@ -128,7 +128,8 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
     };
     __shared__ Shared sh;
     struct Book {
-        uint32_t cnt;   // results of the staged instance not yet added to its count
+        uint64_t cnt;   // results of the staged instance not yet added to its count
+                        // (over any number of items: 32 bits could wrap)
         uint32_t n[8];  // statistics, in the order of d_stats
     };
     __shared__ Book s_book[512 / 64];
@@ -172,8 +173,7 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
     uint32_t lvst = 0, lvw = 0;
     uint64_t lvx = 0, lvwx = 0;
     uint32_t turn = 0;  // blocks of groups done: which dense mask is in use
-    // nodes expanded (for the statistics) and results of the staged instance
-    uint32_t n12 = 0, n6 = 0, n0 = 0, nres = 0;
+    uint32_t n12 = 0, n6 = 0, n0 = 0;  // nodes expanded (for the statistics)
     auto tally = [&](int i, uint32_t v) {  // (an LDS add that nothing waits for)
         if (lane_now() == 0)
             __hip_atomic_fetch_add(&bk.n[i], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -184,6 +184,7 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
             uint64_t n = 0;
             for (int q = 0; q < nw; ++q) {
                 n += s_book[q].cnt;
+                s_book[q].cnt = 0;
             }
             if (n) add64(a.counts + staged, n);
             sh.results += n;
@@ -346,8 +347,6 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
                 continue;
             }
             if (fresh) {
-                bk.cnt = nres;
-                nres = 0;
                 __syncthreads();  // every wave is done with the last instance
                 flush_counts();
                 tab = ntab;
@@ -797,10 +796,10 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
                         // workgroup has used, to a.chunk; the plain mode (0)
                         // reserves exactly.
                         const uint32_t nbal = (uint32_t)__builtin_popcountll(bal);
-                        nres += nbal;
                         uint64_t pos0 = 0, next = 0;
                         uint32_t room = 0;
                         if (lane_now() == 0) {
+                            __hip_atomic_fetch_add(&bk.cnt, (uint64_t)nbal, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                             const uint32_t most = (uint32_t)a.chunk;
                             if (most == 0) {
                                 next = add64(a.total + TOT_SLOTS, nbal);
@@ -873,7 +872,6 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
         if (mode == 2) __syncthreads();  // every wave has read the claim
     }
     // ---- publish the workgroup's totals and close its block of record slots
-    bk.cnt = nres;
     __syncthreads();
     flush_counts();
     const uint32_t lg = (uint32_t)(sh.block >> 16) & 15u, used = (uint32_t)sh.block & 0xFFFFu;

@@ -63,8 +63,8 @@ constexpr int MAX_CLAIM = 16;                   // items of a claim, at most
 constexpr int HEAD_STRIDE = 16;                 // words from queue head to queue head (128 bytes)
 constexpr int QUEUE_BLOCK = 64;                 // (parts of) items a queue holds in a row
 constexpr int DENSE_GROUP = 16;                 // surviving nodes that make a group dense
-// The base of a block of record slots has 44 bits; the top one stands for a
-// block past the caller's records, of which nothing is written.  (Its other
+// The base of a block of record slots has 44 bits; the top one stands for any
+// block from 2^43 on, past every buffer, of which nothing is written.  (Its other
 // bits still differ from one block to the next, which waiting waves look for.)
 constexpr uint64_t PAST_RECORDS = 1ull << 43;
 
@@ -119,7 +119,8 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
     // its statistics once.
     struct Shared {
         uint64_t block;    // of record slots: base << 20 | log2 size << 16 | used (size 0: none yet)
-        uint64_t taken, results;
+        uint64_t taken;
+        uint64_t results;  // those added to the instances' counts
         uint64_t item, since;  // of the last claim
         uint32_t claim, ticket, queue;
         __attribute__((aligned(16))) wpm_item items[MAX_CLAIM + 1];  // of the last claim
@@ -128,9 +129,12 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
     };
     __shared__ Shared sh;
     struct Book {
-        uint64_t cnt;   // results of the staged instance not yet added to its count
-                        // (over any number of items: 32 bits could wrap)
-        uint32_t n[8];  // statistics, in the order of d_stats
+        // Vectors past every resident ridge group, and results, so far (over
+        // any number of items: 32 bits could wrap).  Those that the rest of the
+        // check rejects are the difference: an LDS add of their own made the
+        // smallest sweep 2% longer.
+        uint64_t past, results;
+        uint32_t n[8];  // other statistics, in the order of d_stats
     };
     __shared__ Book s_book[512 / 64];
     if (threadIdx.x == 0) {
@@ -144,7 +148,7 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
     const int wv = (int)__builtin_amdgcn_readfirstlane((uint32_t)(tid >> 6));
     Book &bk = s_book[wv];
     if ((tid & 63) < 8) bk.n[tid & 63] = 0;
-    bk.cnt = 0;
+    bk.past = bk.results = 0;
     __syncthreads();
     const KArgs &a = s_a;
     auto tid_now = [&]() { return wv * 64 + lane_now(); };
@@ -182,12 +186,9 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
     auto flush_counts = [&]() {  // with every wave past its last result
         if (tid_now() == 0 && staged >= 0) {
             uint64_t n = 0;
-            for (int q = 0; q < nw; ++q) {
-                n += s_book[q].cnt;
-                s_book[q].cnt = 0;
-            }
-            if (n) add64(a.counts + staged, n);
-            sh.results += n;
+            for (int q = 0; q < nw; ++q) n += s_book[q].results;
+            if (n != sh.results) add64(a.counts + staged, n - sh.results);
+            sh.results = n;
         }
     };
     for (int64_t round = 0;; ++round) {
@@ -782,8 +783,9 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
                         if (!pball) continue;
                         const bool ok = properties_pass(tab, head, pass, word4, word1);
                         const uint64_t bal = __builtin_amdgcn_ballot_w64(ok);
-                        tally(1, (uint32_t)__builtin_popcountll(pball));
-                        tally(2, (uint32_t)__builtin_popcountll(pball & ~bal));
+                        if (lane_now() == 0)
+                            __hip_atomic_fetch_add(&bk.past, (uint64_t)__builtin_popcountll(pball), __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_WORKGROUP);
                         if (!bal) continue;
                         // Record slots from the workgroup's block.  The wave
                         // whose results cross its end takes what is left, gets
@@ -799,7 +801,7 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
                         uint64_t pos0 = 0, next = 0;
                         uint32_t room = 0;
                         if (lane_now() == 0) {
-                            __hip_atomic_fetch_add(&bk.cnt, (uint64_t)nbal, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                            __hip_atomic_fetch_add(&bk.results, (uint64_t)nbal, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                             const uint32_t most = (uint32_t)a.chunk;
                             if (most == 0) {
                                 next = add64(a.total + TOT_SLOTS, nbal);
@@ -832,7 +834,7 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
                                                            __HIP_MEMORY_SCOPE_WORKGROUP);
                                         asm volatile("" ::: "memory");
                                         uint64_t base = next & (PAST_RECORDS - 1);
-                                        if (next >= a.cap) base |= PAST_RECORDS;
+                                        if (next >= PAST_RECORDS) base |= PAST_RECORDS;
                                         __hip_atomic_store(&sh.block, base << 20 | (uint64_t)l2 << 16 | over,
                                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                                     }
@@ -885,7 +887,8 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
     if (tid == 0 && sh.results) add64(a.total + TOT_RESULTS, sh.results);
     if (a.stats && tid < 8) {
         uint64_t n = 0;
-        for (int q = 0; q < nw; ++q) n += s_book[q].n[tid];
+        for (int q = 0; q < nw; ++q) n += tid == 1 || tid == 2 ? s_book[q].past : s_book[q].n[tid];
+        if (tid == 2) n -= sh.results;
         if (n) add64(a.stats + tid, n);
     }
 }

@@ -432,7 +432,7 @@ typedef struct wpm_sched {
     int32_t grid;              /* persistent modes: workgroups (0 = occupancy x CUs) */
     int32_t flags;             /* WPM_FLAG_* */
     const wpm_item *d_items;   /* device: the items */
-    const wpm_item *h_items;   /* host copy (PLAIN mode launches per instance from it) */
+    const wpm_item *h_items;   /* host copy, read in PLAIN mode alone (it launches per instance from it) */
     int64_t num_items;
     uint32_t *d_scratch;       /* device: >= 4 words (queue heads), cleared by the call */
     uint64_t *d_item_times;    /* optional device [num_items][2]: start, end (s_memrealtime) */

@@ -172,14 +172,6 @@ int enumerate_with(const wpm_batch *b, const wpm_sched *s, uint64_t *d_surv, uin
     // Persistent workgroups reserve record slots in blocks of at most 128 per
     // wave (few global atomics); the one-shot ones of the plain mode reserve
     // exactly.
-    // (the length of the items, by a look at some of them: parts are not
-    // made shorter than the descent splits)
-    uint64_t item_len = 0;
-    if (s->h_items && s->mode != WPM_SCHED_PLAIN)
-        for (int64_t i = 0; i < s->num_items; i += std::max<int64_t>(1, s->num_items / 32)) {
-            const wpm_item &im = s->h_items[i];
-            if (im.cbits <= WPM_MAX_K - 10) item_len = std::max(item_len, (uint64_t)im.lanes << im.cbits);
-        }
     auto launch = [&](int64_t want_grid) -> hipError_t {
         if (tree) {
             KArgs t = a;
@@ -190,12 +182,14 @@ int enumerate_with(const wpm_batch *b, const wpm_sched *s, uint64_t *d_surv, uin
             t.count_bad = !walk;
             t.alone = !walk;
             if (t.mode == 1 || t.mode == 2) {
-                // Fewer items than workgroups: hand each out in parts (stamped
-                // items stay whole).  No workgroup without work.
+                // Fewer items than workgroups: hand each out in parts, one to a
+                // workgroup (stamped items stay whole).  The items are in
+                // device memory, so their lengths are not known here: the
+                // descent keeps TREE_MIN_SPLIT vectors to a part, and the
+                // workgroups of the parts that a short item does not have end
+                // at once.
                 if (!t.times)
-                    while (t.split < 6 && item_len >> (t.split + 1) >= (uint64_t)TREE_MIN_SPLIT &&
-                           (t.num_items << (t.split + 1)) <= grid)
-                        ++t.split;
+                    while (t.split < 6 && (t.num_items << (t.split + 1)) <= grid) ++t.split;
                 const int64_t parts = t.num_items << t.split;
                 grid = std::min<int64_t>(grid, parts);
             }

@@ -308,6 +308,20 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
             const int c = (int)__builtin_amdgcn_readfirstlane((uint32_t)itm.cbits);
             const int lanes = (int)__builtin_amdgcn_readfirstlane((uint32_t)itm.lanes);
             const uint64_t first = rfl64(itm.first);
+            // Parts p..p1 of an item with first index lo and n + 1 vectors; past
+            // its end they are empty.
+            auto part_range = [&](uint64_t lo, uint64_t n, uint32_t p, uint32_t p1, uint64_t &b, uint64_t &e) {
+                uint64_t q = ((n >> split) + 128) & ~127ull;
+                if (q < (uint64_t)TREE_MIN_SPLIT) q = TREE_MIN_SPLIT;
+                b = lo + q * p;
+                e = p1 != (1u << split) - 1u && q * (p1 + 1) <= n ? lo + q * (p1 + 1) - 1 : lo + n;
+                return p == 0 || q * p <= n;
+            };
+            const uint64_t len = c < 64 ? ((uint64_t)lanes << c) - 1 : ~0ull;  // (less one)
+            if (part != 0) {  // an empty part: before anything is staged for it
+                uint64_t b, e;
+                if (!part_range(0, len, part, part, b, e)) continue;
+            }
             auto fits = [&](int cc, int ll, uint64_t ff) {
                 return cc >= 7 && cc <= kp && ll >= 1 && ll <= bd &&
                        (int)(ff & ((1u << LANE_BITS) - 1)) + ll <= (1 << LANE_BITS) &&
@@ -392,16 +406,7 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
             }
             // ---- the run: Gray indices [i0, i1] of this item's parts in the
             // claim, and of the claim's next items while they continue the
-            // range (one set-up for all).  Parts p..p1 of an item with first
-            // index lo and n + 1 vectors; past its end they are empty.
-            auto part_range = [&](uint64_t lo, uint64_t n, uint32_t p, uint32_t p1, uint64_t &b, uint64_t &e) {
-                uint64_t q = ((n >> split) + 128) & ~127ull;
-                if (q < (uint64_t)TREE_MIN_SPLIT) q = TREE_MIN_SPLIT;
-                if (split == 0) q = n;  // one part
-                b = lo + q * p;
-                e = split != 0 && n / q > p1 ? lo + q * (p1 + 1) - 1 : lo + n;
-                return p == 0 || q * p <= n;
-            };
+            // range (one set-up for all).
             const uint32_t plast = (1u << split) - 1u;
             const uint64_t lo0 = c < 64 ? first << c : 0;
             uint64_t i0, i1;
@@ -409,7 +414,7 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
             {
                 const int64_t left = vend - vt - 1;
                 const uint32_t p1 = (int64_t)(plast - part) <= left ? plast : part + (uint32_t)left;
-                some = part_range(lo0, (c < 64 ? ((first + (uint64_t)lanes) << c) - 1 : ~0ull) - lo0, part, p1, i0, i1);
+                some = part_range(lo0, len, part, p1, i0, i1);
                 if (!timed) vt += p1 - part;
             }
             // the list is emptied when the instance or the claim ends

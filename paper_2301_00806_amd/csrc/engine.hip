@@ -261,9 +261,10 @@ int scratch_on_current_device(uint64_t **out) {
 
 int enumerate(const wpm_batch *b, const wpm_sched *s, uint64_t *d_surv, uint64_t cap,
               uint64_t *d_counts, uint64_t *d_total, uint64_t *d_stats, void *stream) {
-    if (!s || s->scratch_words < 0) return WPM_EINVAL;
-    return enumerate_with(b, s, d_surv, cap, d_counts, d_total, d_stats, (uint64_t *)s->d_scratch,
-                          std::max(4, s->scratch_words) / 2, stream);
+    if (!s) return WPM_EINVAL;
+    // (the field was reserved once: whatever else it holds means 4 words)
+    const int64_t words = s->scratch_words == WPM_QUEUE_SCRATCH_WORDS ? WPM_QUEUE_SCRATCH_WORDS : 4;
+    return enumerate_with(b, s, d_surv, cap, d_counts, d_total, d_stats, (uint64_t *)s->d_scratch, words / 2, stream);
 }
 
 int enumerate_noalloc(const wpm_batch *b, const wpm_sched *s, uint64_t *d_surv, uint64_t cap,

@@ -49,3 +49,19 @@ for mode in (L.SCHED_STATIC, L.SCHED_DYNAMIC, L.SCHED_PACKED):
 assert enumerate(mode=L.SCHED_PLAIN, h_items=None) == L.WPM_EINVAL
 print("fine")
 """)
+
+
+def test_scratch_beyond_four_words_only_where_it_is_said_exactly(so):
+    # The field was reserved: a caller that left something in it is neither
+    # refused nor written to beyond its 4 words.
+    check(so, r"""
+for sw in (0, 4, -1, -2**31, 1, 5, 287, 289, 1000, 2**31 - 1, 288):
+    before = len(hip.launches())
+    assert enumerate(num_items=1000, scratch_words=sw) == L.WPM_OK, sw
+    clear, tree, walk = hip.launches()[before:]
+    assert clear[0] == "" and "tree_kernel" in tree[0] and "sweep_kernel" in walk[0]
+    cleared = int.from_bytes(clear[4][5][:8], "little")
+    queues = int.from_bytes(tree[4][3][116:120], "little")
+    assert (cleared, queues) == ((144, 8) if sw == 288 else (2, 1)), (sw, cleared, queues)
+print("fine")
+""")

@@ -399,7 +399,7 @@ def main():
     waves_used = args.waves if args.waves in (7, 8) else 8
     dom_preps = [p for p, c in zip(preps, batch.cls) if int(c) == dom and p.k > 0]
     kinds = {"sweep_kernel<%d>" % waves_used if walked(p) else "tree_kernel<7>" for p in dom_preps}
-    dom_name = "%s (rows of at most %d words)" % (" + ".join(sorted(kinds)), dom)
+    dom_name = "%s (rows of at most %d words)" % (" + ".join(sorted(kinds)), E.class_row_words(dom))
     log(f"dominant launch {dom_name}: {cls_vec[dom]:.4e} vectors in {dom_ms:.2f} ms "
         f"({cls_vec[dom] / dom_ms * 1e3:.3e} vectors/s); per-class ms {seg_ms}")
     out = {}

@@ -168,7 +168,7 @@ int enumerate_with(const wpm_batch *b, const wpm_sched *s, uint64_t *d_surv, uin
     a.split = 0;
     const dim3 block((unsigned)s->wg_size);
     // One launch of each kernel the batch needs over [item_base, num_items);
-    // each takes the items of its tables (malformed items are counted once).
+    // each takes the items of its tables and counts the malformed ones among them.
     // Persistent workgroups reserve record slots in blocks of at most 128 per
     // wave (few global atomics); the one-shot ones of the plain mode reserve
     // exactly.

@@ -329,7 +329,8 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
             };
             // ---- a new instance: its header, counts of the last one, tables.
             // Malformed items are skipped and counted (as in the walk); items
-            // of tables without a level section belong to the walk.
+            // of tables without a level section belong to the walk, which
+            // counts its own.
             bool bad = false, skip = false;
             const bool fresh = (int64_t)inst != staged;
             const uint32_t *ntab = tab;
@@ -355,8 +356,9 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
             bad = bad || !fits(c, lanes, first);
             if (bad || skip) {
                 kp = okp;
-                if (bad && part == 0 && tid_now() == 0) {
-                    if (a.count_bad) add64(a.total + TOT_BAD_ITEMS, 1ull);
+                const bool theirs = inst >= (uint32_t)a.num_instances ? !a.count_bad : skip && !a.alone;
+                if (bad && !theirs && part == 0 && tid_now() == 0) {
+                    add64(a.total + TOT_BAD_ITEMS, 1ull);
                     if (timed) a.times[2 * it] = a.times[2 * it + 1] = 0;
                 }
                 continue;

@@ -307,15 +307,32 @@ LDS_CLASSES = (44, 64, 96, L.MAX_ROW_WORDS)
 
 
 def lds_class(info) -> int:
-    """The launch class of an instance: the smallest row-width bound of
-    LDS_CLASSES that holds its table rows."""
+    """The row width class of an instance: the smallest bound of LDS_CLASSES
+    that holds its table rows."""
     return next(c for c in LDS_CLASSES if info.row_words <= c)
+
+
+def descended(p) -> bool:
+    """Has this instance's table a level section (swept by tree descent)?"""
+    return bool(int(p.table[11]) & 2)
 
 
 def _sweep_kind(members) -> int:
     """wpm_batch flags: whether all tables, or none, have a level section."""
-    kinds = {bool(int(p.table[11]) & 2) for p in members}
+    kinds = {descended(p) for p in members}
     return L.BATCH_TREE if kinds == {True} else L.BATCH_WALK if kinds == {False} else 0
+
+
+def launch_class(p) -> int:
+    """The launch class of an instance: its row width class, plus 1 when its
+    table is walked.  Each class is swept by one kernel over its own items: a
+    class with tables of both kinds would have both look at all of them."""
+    return lds_class(p.info) + (0 if descended(p) else 1)
+
+
+def class_row_words(cls: int) -> int:
+    """The row width that bounds a launch class."""
+    return cls & ~3
 
 
 class DeviceBatch:
@@ -350,7 +367,7 @@ class DeviceBatch:
                 else:
                     self.blocks[i].k = p.k
                     self.blocks[i].free_dims = p.k
-        self.cls = np.array([lds_class(p.info) for p in self.preps], dtype=np.int64)
+        self.cls = np.array([launch_class(p) for p in self.preps], dtype=np.int64)
         self.c_batch = self._batch_of(self.preps)
         self.class_batches = {int(c): self._batch_of([p for p, q in zip(self.preps, self.cls) if q == c])
                               for c in np.unique(self.cls)}

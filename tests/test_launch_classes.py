@@ -1,0 +1,49 @@
+"""Launch classes of a batch: each holds tables of one kind, so that no launch
+looks at the items of the other kernel (host logic, no GPU)."""
+import numpy as np
+import pytest
+
+import wpm_inputs as W
+from paper_2301_00806_amd import _lib as L
+from paper_2301_00806_amd import engine as E
+
+
+@pytest.fixture(scope="module")
+def preps():
+    # convenient bases with few free coordinates: some tables have no level section
+    insts = [i for i in W.batch(E.kdim, count=96) if i.meta["k"] <= 22][:48]
+    out = E.prepare_many(insts, prune=True, min_free=7)
+    assert {E.descended(p) for p in out} == {True, False}
+    return out
+
+
+def test_classes_hold_one_kind(preps):
+    batch = E.DeviceBatch(preps, device="cpu")
+    assert batch.c_batch.flags == 0
+    for c, b in batch.class_batches.items():
+        kinds = {E.descended(p) for p, q in zip(preps, batch.cls) if q == c}
+        assert len(kinds) == 1
+        assert b.flags == (L.BATCH_TREE if kinds == {True} else L.BATCH_WALK)
+        assert E.class_row_words(c) in E.LDS_CLASSES
+        assert b.max_row_words <= E.class_row_words(c)
+    assert len(batch.class_batches) >= 2
+
+
+def test_items_are_split_by_kind(preps):
+    batch = E.DeviceBatch(preps, device="cpu")
+    items = E.build_queue(batch.k, 9, 64, blocks=batch.blocks)
+    out, segs = E.split_by_class(batch, items)
+    assert sorted(map(tuple, out.tolist())) == sorted(map(tuple, items.tolist()))
+    assert len(segs) == len(batch.class_batches)
+    for s in segs:
+        part = out[s.start:s.end]["instance"]
+        assert {E.descended(preps[i]) for i in part} == {batch.class_batches[s.cls].flags == L.BATCH_TREE}
+
+
+def test_one_kind_keeps_the_width_classes():
+    insts = [i for i in W.batch(E.kdim, count=32) if i.meta["k"] <= 22]
+    plain = E.prepare_many(insts)
+    batch = E.DeviceBatch(plain, device="cpu")
+    assert all(E.descended(p) for p in plain)
+    assert np.array_equal(batch.cls, [E.lds_class(p.info) for p in plain])
+    assert batch.c_batch.flags == L.BATCH_TREE

@@ -169,12 +169,10 @@ __device__ __forceinline__ uint32_t hword(const uint32_t *tab, int i) {
 }
 
 // Ridge groups g0, g0 + 1, ... of the entries still passing, in decreasing
-// rejection order, stopping once no entry of the wave passes.  word4(off)
-// gives four consecutive state words of the lane's entry, head(i) a field of
-// the table's header.
-template <class H, class W4>
-__device__ __forceinline__ bool groups_pass(H head, bool pass, int g0, W4 word4) {
-    const int Gp = (int)head(D_G), Qs = (int)head(D_QS);
+// rejection order, stopping once no entry of the wave passes.  Gp groups of
+// stride Qs; word4(off) gives four consecutive state words of the lane's entry.
+template <class W4>
+__device__ __forceinline__ bool groups_pass(int Gp, int Qs, bool pass, int g0, W4 word4) {
 #pragma unroll 1
     for (int g = g0; g < Gp; ++g) {
         if (__builtin_amdgcn_ballot_w64(pass) == 0) break;
@@ -205,10 +203,12 @@ __device__ __forceinline__ bool groups_pass(H head, bool pass, int g0, W4 word4)
 // property of Section 4.2), further affine properties
 // g(K) = c0 + sum_c w_c |K & mask_c| > 0 (Section 2.1) and the deferred ridges
 // (degree <= 2 read off the facet words: parent count, then the parents'
-// facet indices, per ridge).
+// facet indices, per ridge).  head(i) is a field of the table's header, a load
+// from memory in the walk: its caller has Gp and Qs already.
 template <class H, class W4, class W1>
-__device__ __forceinline__ bool properties_pass(const uint32_t *tab, H head, bool pass, W4 word4, W1 word1) {
-    const int Wp = (int)head(D_W), ko = 4 + ((int)head(D_G) - 1) * (int)head(D_QS);
+__device__ __forceinline__ bool properties_pass(const uint32_t *tab, H head, int Gp, int Qs, bool pass, W4 word4,
+                                                W1 word1) {
+    const int Wp = (int)head(D_W), ko = 4 + (Gp - 1) * Qs;
     uint32_t cntf = 0;
 #pragma unroll 1
     for (int w = 0; w < Wp; w += 4) {
@@ -679,7 +679,8 @@ void sweep_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict
                                             wbase + (int)own < (int)__builtin_amdgcn_readfirstlane((uint32_t)ci.lanes);
                                 auto w4 = [&](int off) { return word4(lo, so, off); };
                                 auto w1 = [&](int off) { return word1(lo, so, off); };
-                                pass = groups_pass(hv, pass, 1, w4);
+                                const int Gp = (int)hv(D_G), Qs = (int)hv(D_QS);
+                                pass = groups_pass(Gp, Qs, pass, 1, w4);
                                 // Gray index of the owner's step (the chunk
                                 // start is recomputed, not held through phase 1)
                                 const uint64_t f0 = rfl64(ci.first);
@@ -691,7 +692,7 @@ void sweep_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict
                                 const bool offs = (hv(D_FLAGS) & D_FLAG_OFFSET) != 0u;
                                 pass = pass && (x != 0 || offs) && (kk >= 64 || (x >> kk) == 0);
                                 if (__builtin_amdgcn_ballot_w64(pass)) {
-                                    const bool ok = properties_pass(tab, hv, pass, w4, w1);
+                                    const bool ok = properties_pass(tab, hv, Gp, Qs, pass, w4, w1);
                                     const uint64_t pball = __builtin_amdgcn_ballot_w64(pass);
                                     const uint64_t bal = __builtin_amdgcn_ballot_w64(ok);
                                     bk.n_ridge += (uint32_t)__builtin_popcountll(pball);

@@ -739,7 +739,7 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
                                    hp = __builtin_amdgcn_readfirstlane(h3.x), hn = __builtin_amdgcn_readfirstlane(h3.y),
                                    hd0 = __builtin_amdgcn_readfirstlane(h3.z), hdn = __builtin_amdgcn_readfirstlane(h3.w);
                     auto head = [&](int i) -> uint32_t {
-                        return i == D_K ? hk : i == D_W ? hw : i == D_G ? hg : i == D_QS ? hq : i == D_MAXF ? hm
+                        return i == D_K ? hk : i == D_W ? hw : i == D_MAXF ? hm
                                : i == D_FLAGS ? hf : i == D_PROPS ? hp : i == D_NPROPS ? hn : i == D_DEFER ? hd0 : hdn;
                     };
 #pragma unroll 1
@@ -779,7 +779,7 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
                             for (int b = 0; b < WIN_BITS / 3; ++b) r ^= lds_X[o[b] + off];
                             return r;
                         };
-                        bool pass = groups_pass(head, base + ln < tcnt, 0, word4);
+                        bool pass = groups_pass((int)hg, (int)hq, base + ln < tcnt, 0, word4);
                         const uint64_t i = (twin << WIN_BITS) + (uint64_t)ent;
                         const uint64_t x = i ^ (i >> 1);
                         // x = 0 is the empty complex, except in a coset (K = K*)
@@ -788,7 +788,7 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
                                (kk >= 64 || (x >> kk) == 0);
                         const uint64_t pball = __builtin_amdgcn_ballot_w64(pass);
                         if (!pball) continue;
-                        const bool ok = properties_pass(tab, head, pass, word4, word1);
+                        const bool ok = properties_pass(tab, head, (int)hg, (int)hq, pass, word4, word1);
                         const uint64_t bal = __builtin_amdgcn_ballot_w64(ok);
                         if (lane_now() == 0)
                             __hip_atomic_fetch_add(&bk.past, (uint64_t)__builtin_popcountll(pball), __ATOMIC_RELAXED,

@@ -425,6 +425,11 @@ typedef struct wpm_batch {
 #define WPM_BATCH_WALK 2 /* none has */
 
 #define WPM_FLAG_ACCUMULATE 1 /* do not clear d_counts, d_total, d_stats: add to them */
+/* Every table is walked, whether it has a level section or not (the same
+ * results).  Faster in the static and packed modes for many items (2^15 and
+ * more, 64 and more an instance) of fewer than 64 vectors per lane of a
+ * workgroup: the descent's set-up of an item then costs more than it saves. */
+#define WPM_FLAG_WALK 2
 
 typedef struct wpm_sched {
     int32_t mode;              /* WPM_SCHED_* */

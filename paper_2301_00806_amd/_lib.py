@@ -9,7 +9,7 @@ LIB_PATH = os.path.join(HERE, "libwpm.so")
 
 WPM_OK, WPM_EINVAL, WPM_ECAP, WPM_EKMAX, WPM_EHIP, WPM_ELIMIT = 0, -1, -2, -3, -4, -5
 SCHED_PLAIN, SCHED_STATIC, SCHED_DYNAMIC, SCHED_PACKED = 0, 1, 2, 3
-FLAG_ACCUMULATE = 1
+FLAG_ACCUMULATE, FLAG_WALK = 1, 2
 BATCH_TREE, BATCH_WALK = 1, 2
 CX_FULL_PICARD, CX_SEED = 1, 2
 TOTAL_WORDS = 4

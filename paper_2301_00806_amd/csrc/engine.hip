@@ -79,21 +79,21 @@ int device_query(int32_t *num_cus, int64_t *wallclock_khz, int32_t *lds_per_bloc
     return WPM_OK;
 }
 
-int persistent_grid_waves(const wpm_batch *b, int wg_size, int waves, int32_t *grid);
+int persistent_grid_waves(const wpm_batch *b, int wg_size, int waves, bool tree, int32_t *grid);
 
 int persistent_grid(const wpm_batch *b, int wg_size, int32_t *grid) {
-    return persistent_grid_waves(b, wg_size, 0, grid);
+    return b ? persistent_grid_waves(b, wg_size, 0, wants_tree(b), grid) : WPM_EINVAL;
 }
 
-int persistent_grid_waves(const wpm_batch *b, int wg_size, int waves, int32_t *grid) {
-    if (!b || !grid || wg_size < 64 || wg_size > 512 || (wg_size % 64)) return WPM_EINVAL;
+int persistent_grid_waves(const wpm_batch *b, int wg_size, int waves, bool tree, int32_t *grid) {
+    if (!grid || wg_size < 64 || wg_size > 512 || (wg_size % 64)) return WPM_EINVAL;
     if (b->max_row_words < 4 || b->max_row_words > WPM_MAX_ROW_WORDS || (b->max_row_words & 3)) return WPM_EINVAL;
     if (b->max_kp < 7 || b->max_kp > WPM_MAX_K) return WPM_EINVAL;
     int32_t cus = 0;
     int rc = device_query(&cus, nullptr, nullptr);
     if (rc) return rc;
     int nb = 0;
-    if (wants_tree(b))
+    if (tree)
         HIP_TRY(occupancy_tree(&nb, wg_size, tree_lds_bytes(b->max_kp, b->max_row_words, wg_size)));
     else
         HIP_TRY(occupancy_sweep(pick_waves(waves), &nb, wg_size,
@@ -126,7 +126,8 @@ int enumerate_with(const wpm_batch *b, const wpm_sched *s, uint64_t *d_surv, uin
     hipStream_t st = (hipStream_t)stream;
     const int waves = pick_waves(s->waves_per_simd);
     if ((b->flags & WPM_BATCH_TREE) && (b->flags & WPM_BATCH_WALK)) return WPM_EINVAL;
-    const bool tree = wants_tree(b), walk = wants_walk(b);
+    const bool all = (s->flags & WPM_FLAG_WALK) != 0;
+    const bool tree = wants_tree(b) && !all, walk = wants_walk(b) || all;
     const size_t lds = walk ? sweep_lds_bytes(b->max_kp, b->max_row_words, s->wg_size) : 0;
     const size_t tree_lds = tree ? tree_lds_bytes(b->max_kp, b->max_row_words, s->wg_size) : 0;
     int32_t lds_max = 0;
@@ -201,7 +202,7 @@ int enumerate_with(const wpm_batch *b, const wpm_sched *s, uint64_t *d_surv, uin
             KArgs w = a;
             w.chunk = (s->mode == WPM_SCHED_PLAIN) ? 0 : 128;
             w.count_bad = 1;
-            w.alone = !tree;
+            w.alone = all ? 2 : !tree;
             w.head = a.head ? a.head + 1 : nullptr;
             const int64_t grid = w.mode == 3 ? want_grid : std::min<int64_t>(want_grid, w.num_items - w.item_base);
             return launch_sweep(waves, dim3((unsigned)grid), block, lds, st, b->d_tables, b->d_offsets, s->d_items, w);
@@ -227,7 +228,7 @@ int enumerate_with(const wpm_batch *b, const wpm_sched *s, uint64_t *d_surv, uin
         return WPM_OK;
     }
     int32_t grid = s->grid;
-    if (grid <= 0 && (rc = persistent_grid_waves(b, s->wg_size, waves, &grid))) return rc;
+    if (grid <= 0 && (rc = persistent_grid_waves(b, s->wg_size, waves, tree, &grid))) return rc;
     a.mode = (s->mode == WPM_SCHED_STATIC) ? 1 : (s->mode == WPM_SCHED_DYNAMIC) ? 2 : 3;
     HIP_TRY(launch(grid));
     return WPM_OK;

@@ -93,7 +93,7 @@ struct KArgs {
     int num_instances;
     int max_rs, max_kp;  // the LDS of a workgroup holds tables up to these sizes
     int count_bad;       // items of unknown instances are counted by this launch
-    int alone;           // no launch of the other kernel: its items are malformed
+    int alone;           // no launch of the other kernel: its items are malformed (1), or the walk's too (2)
     int split;           // descent: every item is handed out as 2^split parts
     int queues;          // descent: queue heads (a power of two, 16 words apart)
 };
@@ -379,7 +379,7 @@ void sweep_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict
             Qp = (int)tab[D_QS];
             RS = (int)tab[D_RS];
             has_off = (tab[D_FLAGS] & D_FLAG_OFFSET) != 0u;
-            skip = (tab[D_FLAGS] & D_FLAG_TREE) != 0u;
+            skip = (tab[D_FLAGS] & D_FLAG_TREE) != 0u && a.alone != 2;
             bad = skip && a.alone;
             bad = bad || tab[D_MAGIC] != D_TABLE_MAGIC || kp < 7 || kp > a.max_kp || RS > a.max_rs || (RS & 3) ||
                   G < 1 || (Qp != 4 && Qp != 8) || 4 + (G - 1) * Qp + W > RS || c < 7 || c > kp ||

@@ -438,6 +438,10 @@ class DeviceBatch:
             self._views = (hosts, per)
         return self._views
 
+    def class_size(self, cls: Optional[int]) -> int:
+        """Instances of a launch class (None: of the batch)."""
+        return len(self.cls) if cls is None else int(np.count_nonzero(self.cls == cls))
+
     def class_grid(self, cls: int, wg_size: int) -> int:
         """persistent_grid of one launch class, cached per workgroup size."""
         if getattr(self, "_grids", None) is None:
@@ -523,10 +527,15 @@ def pack_bins(items: np.ndarray, bins: int, cost: Optional[np.ndarray] = None):
     return arr, offs, mx.value
 
 
-def persistent_grid(batch: "DeviceBatch", wg_size: int, cls: Optional[int] = None) -> int:
+def persistent_grid(batch: "DeviceBatch", wg_size: int, cls: Optional[int] = None,
+                    walk: bool = False) -> int:
     """Workgroups of a persistent launch (of one launch class, or of the
-    whole batch with the LDS layout of its widest table)."""
+    whole batch with the LDS layout of its widest table); with `walk`, of one
+    that walks every table."""
     cb = batch.c_batch if cls is None else batch.class_batches[int(cls)]
+    if walk:
+        cb = L.Batch.from_buffer_copy(cb)
+        cb.flags = L.BATCH_WALK
     g = ctypes.c_int32(0)
     L.check("wpm_persistent_grid", L.lib().wpm_persistent_grid(ctypes.byref(cb), wg_size,
                                                                ctypes.byref(g)))
@@ -588,6 +597,27 @@ def class_items(batch: "DeviceBatch", cbits: int, lanes: int, cost: Optional[np.
     return items, segs
 
 
+def walks_short_items(items: np.ndarray, wg_size: int, instances: int) -> bool:
+    """Is a static or packed launch of these items of so many instances better walked?  The descent
+    sets an item up with every wave, whatever it holds, and only the dynamic
+    queue hands out neighbours together, which share a set-up.  So where
+    items hold fewer than 64 vectors per lane of their workgroup, on average, the
+    walk is faster, once there are many of them (2^15; the walk of fewer is bound
+    by its longest item) and many an instance (64; an instance's tables take the
+    walk longer).  Static sweeps of 256 lanes over convenient bases,
+    walked / descended, ms: 4.7e6 items of 2^10 vectors 20.0 / 28.6, 1.3e6 of
+    2^12 6.3 / 9.4, 68e3 of 2^13 0.73 / 0.95; not so 31e3 of 2^14 0.87 / 0.60,
+    15e3 of 2^10 0.22 / 0.17, 23e3 of 2^7, 61 an instance, 0.60 / 0.35."""
+    n = len(items)
+    if n < 1 << 15:
+        return False
+    part = items[::n // 1024]
+    vectors = np.ldexp(part["lanes"].astype(np.float64), part["cbits"].astype(np.int64))
+    if float(vectors.mean()) >= 64.0 * wg_size:
+        return False
+    return n >= 64 * instances
+
+
 @dataclass
 class SweepResult:
     counts: np.ndarray
@@ -624,6 +654,7 @@ class Sweeper:
         self._items_dev = None
         self._items_host = None
         self._items_ptr = 0
+        self._walked = {}
         self._times = None
         self._segments = []
         self._seg_bins = []
@@ -647,6 +678,7 @@ class Sweeper:
             pinned = None   # a view into the pinned array: copied the plain way
         self._items_host = items if pinned is not None else np.ascontiguousarray(items)
         self._items_ptr = self._items_host.ctypes.data if len(items) else 0
+        self._walked = {}
         self._segments = segments
         self._seg_bins = [None if sg.bins is None else torch.from_numpy(
             np.ascontiguousarray(sg.bins, np.int64)).to(self.device) for sg in segments]
@@ -661,6 +693,16 @@ class Sweeper:
             self._items_dev = torch.from_numpy(raw.copy()).to(self.device)
         self._times = (torch.zeros((max(1, len(items)), 2), dtype=torch.int64, device=self.device)
                        if want_times else None)
+
+    def _walks(self, seg, mode: int, wg_size: int) -> bool:
+        """walks_short_items of a segment, looked up once for its items."""
+        if mode not in (L.SCHED_STATIC, L.SCHED_PACKED) or not self._items_ptr:
+            return False
+        key = (seg.start, seg.end, wg_size)
+        if key not in self._walked:
+            self._walked[key] = walks_short_items(self._items_host[seg.start:seg.end], wg_size,
+                                                  self.batch.class_size(seg.cls))
+        return self._walked[key]
 
     def launch(self, mode: int, wg_size: int = 256, grid: int = 0, stream=None,
                seg_events: bool = False, accumulate: bool = False, waves: int = 0) -> None:
@@ -682,7 +724,8 @@ class Sweeper:
             n = sg.end - sg.start
             bins = self._seg_bins[i] if self._segments else None
             s = L.Sched(mode=mode, wg_size=wg_size, grid=grid,
-                        flags=L.FLAG_ACCUMULATE if (i or accumulate) else 0,
+                        flags=(L.FLAG_ACCUMULATE if (i or accumulate) else 0) |
+                        (L.FLAG_WALK if self._walks(sg, mode, wg_size) else 0),
                         d_items=self._items_dev.data_ptr() + 16 * sg.start,
                         h_items=self._items_ptr + 16 * sg.start if n else None,
                         num_items=n, d_scratch=self.scratch.data_ptr(),
@@ -756,7 +799,7 @@ class Sweeper:
             cb = self.batch.c_batch if sg.cls is None else self.batch.class_batches[sg.cls]
             n = a1 - a0
             s = L.Sched(mode=mode, wg_size=wg_size, grid=grid,
-                        flags=L.FLAG_ACCUMULATE if r else 0,
+                        flags=(L.FLAG_ACCUMULATE if r else 0) | (L.FLAG_WALK if self._walks(sg, mode, wg_size) else 0),
                         d_items=self._items_dev.data_ptr() + 16 * a0,
                         h_items=items.ctypes.data + 16 * a0 if n else None,
                         num_items=n, d_scratch=self.scratch.data_ptr(),

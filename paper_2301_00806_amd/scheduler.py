@@ -70,8 +70,9 @@ def make_plan(batch: "E.DeviceBatch", policy: str, cost: Optional[np.ndarray] = 
     if policy == "packed":
         parts, out_segs, pos, mk = [], [], 0, 0.0
         for sg in segs:
-            bins = E.persistent_grid(batch, wg, sg.cls)
-            it, offs, mx = E.pack_bins(items[sg.start:sg.end], bins, c)
+            part = items[sg.start:sg.end]
+            bins = E.persistent_grid(batch, wg, sg.cls, E.walks_short_items(part, wg, batch.class_size(sg.cls)))
+            it, offs, mx = E.pack_bins(part, bins, c)
             parts.append(it)
             out_segs.append(E.Segment(sg.cls, pos, pos + len(it), offs))
             pos += len(it)

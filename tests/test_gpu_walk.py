@@ -101,3 +101,47 @@ def test_mixed_launch(E, mode, grid, cbits):
         assert len(rec) == tot[0]
         uniq, times = np.unique(rec, axis=0, return_counts=True)
         assert (times == rep).all() and len(uniq) == sum(map(len, want))
+
+
+# ------------------------------------------ descended tables under the walk
+
+@pytest.mark.parametrize("mode", [1, 2, 3])
+def test_walk_flag_gives_the_same_sweep(E, mode):
+    # tables of both kinds, walked in one launch
+    from paper_2301_00806_amd import _lib as L
+    preps = mixed(E)
+    batch = E.DeviceBatch(preps)
+    items = E.build_queue(batch.k, 9, 128)
+    bins = torch.from_numpy(np.linspace(0, len(items), 6).astype(np.int64)).to("cuda")
+    sw = E.Sweeper(batch, cap=1 << 20)
+    sw.set_items(items, split_classes=False)
+    for flags in (0, L.FLAG_WALK):
+        s = L.Sched(mode=mode, wg_size=128, grid=5, flags=flags, d_items=sw._items_dev.data_ptr(),
+                    num_items=len(items), d_scratch=sw.scratch.data_ptr(), d_bin_offsets=bins.data_ptr())
+        L.check("enumerate", L.lib().wpm_enumerate(
+            ctypes.byref(batch.c_batch), ctypes.byref(s), sw.surv.data_ptr(), sw.cap, sw.counts.data_ptr(),
+            sw.total.data_ptr(), sw.stats.data_ptr(), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)))
+        res = sw.result()
+        assert (res.stats[5:8] == 0).all() == (flags == L.FLAG_WALK)
+        assert sw.collect() == oracle_sets(preps)
+
+
+@pytest.mark.parametrize("mode", [1, 3])
+def test_short_items_are_walked_in_static_and_packed_launches(E, mode):
+    from paper_2301_00806_amd import scheduler as S
+    insts = [i for i in W.batch(E.kdim, count=160) if 16 < i.meta["k"] <= 24]
+    preps = E.prepare_many(insts, prune=True, min_free=7)
+    preps = [p for p in preps if E.descended(p)]
+    batch = E.DeviceBatch(preps)
+    sw = E.Sweeper(batch, cap=1 << 22)
+    plan = S.make_plan(batch, {1: "static", 3: "packed"}[mode], cbits=7, wg=256)
+    assert plan.mode == mode
+    assert [E.walks_short_items(plan.items[s.start:s.end], 256, len(preps)) for s in plan.segments] == [True]
+    want = [O.count_wpm(p.n, [int(f) for f in p.facets], p.max_facets) for p in preps]
+    sw.set_items(plan.items, segments=plan.segments)
+    for _ in range(2):
+        sw.launch(mode, wg_size=256)
+        res = sw.result()
+        assert [int(c) for c in res.counts] == want and (res.stats[5:8] == 0).all()
+    sw.launch_fetch(mode, wg_size=256)
+    assert [int(c) for c in sw.result().counts] == want

@@ -47,3 +47,18 @@ def test_one_kind_keeps_the_width_classes():
     assert all(E.descended(p) for p in plain)
     assert np.array_equal(batch.cls, [E.lds_class(p.info) for p in plain])
     assert batch.c_batch.flags == L.BATCH_TREE
+
+
+@pytest.mark.parametrize("wg", [64, 256, 512])
+def test_walked_short_items(wg):
+    # fewer than 64 vectors per lane of the workgroup on average, 2^15 items and
+    # more, 64 of an instance and more
+    def walked(n, per_instance, lanes, cbits):
+        items = np.zeros(n, dtype=E.ITEM_DTYPE)
+        items["lanes"], items["cbits"] = lanes, cbits
+        return E.walks_short_items(items, wg, -(-n // per_instance))
+    n = 1 << 15
+    assert walked(n, 64, wg - 1, 6) and walked(n + 77, 1 << 20, 1, 6)
+    assert not walked(n, 64, wg, 6) and not walked(n, 64, 1, 63)
+    assert not walked(n - 1, 64, wg - 1, 6) and not walked(0, 64, 1, 7) and not walked(1, 64, 1, 7)
+    assert not walked(n, 63, wg - 1, 6)

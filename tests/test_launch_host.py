@@ -13,8 +13,8 @@ def so(tmp_path_factory):
 COMMON = r"""
 words = np.zeros(64, np.uint64)
 batch = L.Batch(num_instances=1, max_row_words=8, max_kp=24, d_tables=64, d_offsets=64)
-def enumerate(flags=0, **kw):
-    batch.flags = flags
+def enumerate(kind=0, **kw):
+    batch.flags = kind
     a = dict(mode=L.SCHED_DYNAMIC, wg_size=256, grid=0, d_items=64, num_items=5, d_scratch=64, d_bin_offsets=64)
     a.update(kw)
     s = L.Sched(**a)
@@ -63,5 +63,25 @@ for sw in (0, 4, -1, -2**31, 1, 5, 287, 289, 1000, 2**31 - 1, 288):
     cleared = int.from_bytes(clear[4][5][:8], "little")
     queues = int.from_bytes(tree[4][3][116:120], "little")
     assert (cleared, queues) == ((144, 8) if sw == 288 else (2, 1)), (sw, cleared, queues)
+print("fine")
+""")
+
+
+def test_walk_flag_launches_the_walk_alone(so):
+    check(so, r"""
+for mode in (L.SCHED_STATIC, L.SCHED_DYNAMIC, L.SCHED_PACKED):
+    for flags in (0, L.BATCH_TREE, L.BATCH_WALK):
+        for sched in (0, L.FLAG_WALK, L.FLAG_WALK | L.FLAG_ACCUMULATE):
+            before = len(hip.launches())
+            got = enumerate(flags, mode=mode, num_items=9, grid=7, **{"flags": sched})
+            assert got == L.WPM_OK
+            kernels = [l for l in hip.launches()[before:] if l[0]]
+            alone = [int.from_bytes(l[4][3][108:112], "little") for l in kernels]
+            names = ["tree" if "tree_kernel" in l[0] else "walk" for l in kernels]
+            if sched & L.FLAG_WALK:
+                assert (names, alone) == (["walk"], [2])
+            else:
+                assert names == {0: ["tree", "walk"], L.BATCH_TREE: ["tree"], L.BATCH_WALK: ["walk"]}[flags]
+                assert alone == ([1] if flags else [0, 0])
 print("fine")
 """)

@@ -346,7 +346,6 @@ def main():
     torch.cuda.synchronize()
     seg_ms = {(None if cls is None else int(cls)): a0.elapsed_time(a1) for cls, a0, a1 in sw.seg_events}
     assert np.array_equal(sw.counts[:len(preps)].cpu().numpy().astype(np.uint64), res_b.counts)
-    roof_stats = sw.stats.cpu().numpy().astype(np.uint64)
 
     # ---- end to end once: packed tables host -> HBM, one step, records back
     # and expanded into canonical facet lists by wpm_collect
@@ -399,6 +398,12 @@ def main():
     waves_used = args.waves if args.waves in (7, 8) else 8
     dom_preps = [p for p, c in zip(preps, batch.cls) if int(c) == dom and p.k > 0]
     kinds = {"sweep_kernel<%d>" % waves_used if walked(p) else "tree_kernel<7>" for p in dom_preps}
+    # its statistics: the class alone, once more
+    seg = next(s for s in plan.segments if s.cls is None or int(s.cls) == dom)
+    sw.set_items(plan.items[seg.start:seg.end], segments=[E.Segment(seg.cls, 0, seg.end - seg.start, seg.bins)])
+    sw.launch(plan.mode, wg_size=args.wg, stream=stream, waves=args.waves)
+    torch.cuda.synchronize()
+    roof_stats = sw.stats.cpu().numpy().astype(np.uint64)
     dom_name = "%s (rows of at most %d words)" % (" + ".join(sorted(kinds)), E.class_row_words(dom))
     log(f"dominant launch {dom_name}: {cls_vec[dom]:.4e} vectors in {dom_ms:.2f} ms "
         f"({cls_vec[dom] / dom_ms * 1e3:.3e} vectors/s); per-class ms {seg_ms}")
@@ -495,9 +500,7 @@ def main():
             b.copy_(a)
         torch.cuda.synchronize()
 
-    # (the statistics are of all classes, whose other members hold a negligible
-    # share of the work)
-    dom_ops = sweep_ops(preps, roof_stats)
+    dom_ops = sweep_ops(dom_preps, roof_stats)
     achieved = dom_ops / (dom_ms * 1e-3) / 1e12
     # the same launch priced at the plain per-ridge check's work per vector
     # (AND + popcount per parent word of every critical ridge), weighted by 2^k
@@ -509,9 +512,12 @@ def main():
     # the walk's fast step: its instruction-mix ceiling: per vector 4.5 two-source ops
     # (4 XORs, a quarter of a minimum and of a compare) and 2.25 three-source
     # ops (2 logic ops, a quarter of a 3-input minimum) at the probe's rates
-    probe3 = E.valu_probe(1, 8)
-    probe2 = E.valu_probe(0, 8)
-    mix_ceiling = ALG_OPS_PER_VECTOR / (4.5 / probe2 + 2.25 / probe3)
+    # (nothing to compare a descent with)
+    mix_ceiling = None
+    if any(walked(p) for p in dom_preps):
+        probe3 = E.valu_probe(1, 8)
+        probe2 = E.valu_probe(0, 8)
+        mix_ceiling = ALG_OPS_PER_VECTOR / (4.5 / probe2 + 2.25 / probe3)
     def profiled(name):
         path = os.path.join(ROOT, "profiles", name)
         if not os.path.exists(path):
@@ -567,8 +573,8 @@ def main():
                              "of the tests made; effective_plain prices all vectors at the plain per-ridge "
                              "AND+popcount check",
                      "measured_int32_xor_peak": probe / 1e12,
-                     "mix_ceiling": mix_ceiling / 1e12,
-                     "mix_ceiling_frac": mix_ceiling / INT32_PEAK,
+                     "mix_ceiling": None if mix_ceiling is None else mix_ceiling / 1e12,
+                     "mix_ceiling_frac": None if mix_ceiling is None else mix_ceiling / INT32_PEAK,
                      "executed_frac": None if counters is None else
                      counters["executed_lane_ops_per_s"] / INT32_PEAK,
                      "valu_busy": None if counters is None else counters["valu_busy"]},

@@ -489,8 +489,8 @@ int wpm_persistent_grid(const wpm_batch *batch, int32_t wg_size, int32_t *grid);
  *               rejected by the facet bound, the properties or a deferred
  *               ridge, [3] wave passes over the listed candidates, [4] wave
  *               steps whose candidates overflowed the list, [5..7] sub-cubes of
- *               2^18, 2^12 and 2^6 vectors that the descent opened (waves that
- *               share one count it each)
+ *               2^18, 2^12 and 2^6 vectors that the descent opened (one that
+ *               several items touch, once for each run of items)
  * Items must lie inside their instance's 2^max(k,7) Gray range with
  * 7 <= cbits <= max(k, 7), 1 <= lanes <= wg_size, and first mod
  * WPM_LANE_WINDOW + lanes <= WPM_LANE_WINDOW (wpm_build_queue and

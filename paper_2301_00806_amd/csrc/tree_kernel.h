@@ -177,7 +177,6 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
     uint32_t lvst = 0, lvw = 0;
     uint64_t lvx = 0, lvwx = 0;
     uint32_t turn = 0;  // blocks of groups done: which dense mask is in use
-    uint32_t n12 = 0, n6 = 0, n0 = 0;  // nodes expanded (for the statistics)
     auto tally = [&](int i, uint32_t v) {  // (an LDS add that nothing waits for)
         if (lane_now() == 0)
             __hip_atomic_fetch_add(&bk.n[i], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -539,7 +538,7 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
                         const uint32_t nb = ccnt < 64u ? ccnt : 64u;
                         ccnt -= nb;
                         cbase = ccnt;
-                        n0 += nb;
+                        tally(7, nb);
                         const bool mine = (uint32_t)lane_now() < nb;
                         const uint32_t e = mine ? (uint32_t)lds_C[cbase + (uint32_t)lane_now()] : 0u;
                         const uint32_t gr = (e << 6) ^ (e << 5);
@@ -595,7 +594,6 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
                         for (int q = 0; q < 8; ++q) v[q] = o6[q] ^ rlane(o12[q], r12);
                         const uint32_t f = fail4(v[0], v[1], v[2], v[3]) | fail4(v[4], v[5], v[6], v[7]);
                         uint64_t m6 = __builtin_amdgcn_ballot_w64(f == 0u);
-                        ++n6;
                         if (!m6) continue;
                         const uint64_t nb = (gcur << GROUP_BITS) + ((uint64_t)r12 << 12);
                         if (nb < i0 || i1 - nb < 4095) {  // a node that the range only partly covers
@@ -692,11 +690,15 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
 #pragma unroll
                     for (int q = 0; q < 12; ++q) o12[q] ^= rlane(dv, (uint32_t)(DLV_SIX + q));
                     m12 = __builtin_amdgcn_ballot_w64(fail4(o12[8], o12[9], o12[10], o12[11]) == 0u);
-                    ++n12;
                     const uint64_t gb = gcur << GROUP_BITS;
                     if (gb < i0) m12 &= ~0ull << ((i0 - gb) >> 12);
                     if (i1 - gb < (1ull << GROUP_BITS) - 1) m12 &= ~0ull >> (63 - ((i1 - gb) >> 12));
                     const int left = __builtin_popcountll(m12);
+                    // (counted by the wave that expands it, of a shared one by the first)
+                    if ((phase == 1 ? left < DENSE_GROUP : wv == 0) && lane_now() == 0) {
+                        __hip_atomic_fetch_add(&bk.n[5], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        __hip_atomic_fetch_add(&bk.n[6], (uint32_t)left, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
                     share6 = false;
                     if (phase == 1) {
                         if (left >= DENSE_GROUP) {
@@ -884,10 +886,6 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
                 }
             }
         }
-        tally(5, n12);
-        tally(6, n6);
-        tally(7, n0);
-        n12 = n6 = n0 = 0;
         if (mode == 2) __syncthreads();  // every wave has read the claim
     }
     // ---- publish the workgroup's totals and close its block of record slots

@@ -375,6 +375,10 @@ class Buffer {
         }
         return p_ != nullptr;
     }
+    void release() {
+        std::free(p_);
+        p_ = nullptr;
+    }
     T *get() const { return p_; }
     T &operator[](size_t i) const { return p_[i]; }
 
@@ -402,9 +406,10 @@ struct Collected {
     uint32_t *basis = nullptr;  // [k][W] permuted basis rows
     uint32_t *off = nullptr;    // [W] permuted offset (zero for a subspace)
     int64_t first = 0, n = 0;   // results [first, first + n) of the call
-    uint32_t *kv = nullptr;     // [n][W] permuted bit vectors
+    uint32_t *kv = nullptr;     // [n][W] permuted bit vectors (in order, of an instance of one range)
     int buckets = 1;            // key ranges the results are sorted in
     int64_t chunk0 = 0, chunks = 0, bucket0 = 0;
+    int64_t shared0 = 0;        // place of the first result in the arrays of instances of several ranges
     Key *split = nullptr;       // [buckets - 1] first keys of the ranges after the first
     int64_t words = 0;
 };
@@ -483,10 +488,23 @@ inline bool canon_less(const uint32_t *A, const uint32_t *B, int W) {
 
 }  // namespace
 
-// Host expansion of the records into canonical facet lists.  The records are
-// grouped by instance with a counting sort (host threads over slot ranges);
-// each instance then expands its x values into permuted bit vectors, sorts
-// them canonically, and writes [len, facets...] per complex.
+// Host expansion of the records into canonical facet lists, in phases that a
+// team of threads shares:
+//   the records are grouped by instance (histograms of record ranges, scatter);
+//   every result is expanded into a permuted bit vector, and the words of its
+//     list are counted.  An instance of one key range is sorted here, by one
+//     thread in its own memory; in a larger one each result is assigned to one
+//     of up to 256 key ranges, found by a sample, and then put to its range;
+//   the lists' places follow;
+//   the lists are written: an instance of one range as its bit vectors lie,
+//     of a larger one each range is sorted and written.
+// With a batch of many instances the whole is bound by passes over memory, with
+// a single one by its sort.  Instances are cut into ranges from 4096 results
+// on, or from as many as leave every thread 8 instances, at most 16384.  (Keys,
+// references and ranges of every result in memory, 41 bytes each, made the
+// headline batch, 5.4e7 results of 16384 instances on 16 cores, 951 ms, and
+// sorting by instance alone 810; now 715.  128 instances 10.7 -> 8.5 ms, one of
+// 31e3 results 4.1 by instance, 1.11 -> 1.00.)
 int collect(const wpm_host_instance *insts, int32_t num, const uint64_t *d_surv, uint64_t cap,
             const uint64_t *d_counts, const uint64_t *d_total, uint64_t *h_counts, uint32_t *h_out,
             int64_t out_cap, int64_t *out_words, int64_t *h_offsets, void *stream) {
@@ -526,37 +544,33 @@ int collect(const wpm_host_instance *insts, int32_t num, const uint64_t *d_surv,
             rec = rec_copy.get();
         }
     }
-    // Phases, each shared by the team: the records are grouped by instance
-    // (histograms of record ranges, then scatter); every result is expanded
-    // into a permuted bit vector and assigned, in instances with many, to one
-    // of `buckets` key ranges; each bucket is sorted and written.  (By instance
-    // only, with one thread sorting through an index: 23,399 results of one
-    // instance took 3.6 ms, 99,098 of one 3.7 ms, 544,237 of 256 12.5 ms; now
-    // 1.1, 2.4 and 9.5 ms on 16 cores, copy of the records and page faults of
-    // the result included, which bound the last.)
     const int hw = (int)std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
     const int want = (int)std::min<int64_t>(hw, 1 + (int64_t)(slots / 1024) + num / 64);
-    const int64_t ranges = std::max<int64_t>(1, std::min<int64_t>(64, (int64_t)(slots / 8192) + 1));
+    // (no more histograms than there are records for)
+    const int64_t ranges = std::max<int64_t>(
+        1, std::min<int64_t>({64, (int64_t)(slots / 8192) + 1, (int64_t)(slots / std::max<uint64_t>(1, (uint64_t)num))}));
     const uint64_t per = (slots + ranges - 1) / (uint64_t)ranges;
     constexpr int64_t CHUNK = 1024;
     const bool write = h_out != nullptr;
-    struct Task { int32_t inst; int32_t sub; };
+    struct Task { int32_t inst; int32_t sub; };  // sub: a chunk or a range; -1: the whole instance
     struct Cell { int64_t n, words; };
+    struct Ref { Key key; uint32_t idx; };
     std::vector<int64_t> hist;
     std::vector<Collected> cs;
-    struct Ref { Key key; int64_t idx; };
     Buffer<uint64_t> xs;
-    Buffer<Key> keys;
     Buffer<uint32_t> kv;
+    // of the instances of several ranges: each result's range, and the results
+    // range by range
     Buffer<uint8_t> bucket_of;
-    Buffer<Ref> refs;
+    Buffer<uint32_t> order;
     std::vector<uint32_t> facet_words;
     std::vector<Key> splits;
-    std::vector<Task> chunk_tasks, bucket_tasks;
-    std::vector<int64_t> cell0;   // first cell of each chunk task
-    std::vector<Cell> cells;      // per chunk task and bucket
-    std::vector<Cell> starts;     // per bucket task: first result, first word (in the instance)
-    std::atomic<int> bad{0};
+    std::vector<Task> expand_tasks, write_tasks;
+    std::vector<int64_t> cell0;   // first cell of each expand task that is a chunk
+    std::vector<Cell> cells;      // per chunk and range
+    std::vector<Cell> starts;     // per range: first result, first word (in the instance)
+    size_t row_words = 0, rows = 0;  // of a thread's own memory
+    std::atomic<int> bad{0}, failed{0};
     int rc = WPM_OK;
     bool stop = false;
     try {
@@ -567,7 +581,8 @@ int collect(const wpm_host_instance *insts, int32_t num, const uint64_t *d_surv,
     }
     auto plan = [&]() -> int {  // after the histograms, on one thread
         if (bad) return WPM_EINVAL;
-        int64_t total_n = 0, fw = 0, kw = 0, sw = 0;
+        int64_t total_n = 0, fw = 0, kw = 0, sw = 0, shared = 0, nc = 0;
+        const int64_t most = std::min<int64_t>(16 * CHUNK, std::max<int64_t>(4 * CHUNK, (int64_t)total / (8 * want)));
         for (int i = 0; i < num; ++i) {
             int64_t c = 0;
             for (int64_t r = 0; r < ranges; ++r) {
@@ -583,29 +598,37 @@ int collect(const wpm_host_instance *insts, int32_t num, const uint64_t *d_surv,
             ci.n = c;
             total_n += c;
             if (!c) continue;
-            ci.buckets = c > 4 * CHUNK ? (int)std::min<int64_t>(256, c / CHUNK) : 1;
-            ci.chunks = (c + CHUNK - 1) / CHUNK;
-            ci.chunk0 = (int64_t)chunk_tasks.size();
-            ci.bucket0 = (int64_t)bucket_tasks.size();
-            for (int64_t q = 0; q < ci.chunks; ++q) chunk_tasks.push_back({i, (int32_t)q});
-            for (int q = 0; q < ci.buckets; ++q) bucket_tasks.push_back({i, q});
+            if (c > most) {
+                ci.buckets = (int)std::min<int64_t>(256, c / CHUNK);
+                ci.chunks = (c + CHUNK - 1) / CHUNK;
+                ci.chunk0 = (int64_t)expand_tasks.size();
+                ci.bucket0 = (int64_t)starts.size();
+                ci.shared0 = shared;
+                shared += c;
+                for (int64_t q = 0; q < ci.chunks; ++q) {
+                    expand_tasks.push_back({i, (int32_t)q});
+                    cell0.push_back(nc);
+                    nc += ci.buckets;
+                }
+                for (int q = 0; q < ci.buckets; ++q) write_tasks.push_back({i, q});
+                starts.resize(starts.size() + (size_t)ci.buckets, Cell{0, 0});
+            } else {
+                expand_tasks.push_back({i, -1});
+                cell0.push_back(0);
+                write_tasks.push_back({i, -1});
+                row_words = std::max(row_words, (size_t)c * ci.W);
+            }
+            rows = std::max(rows, (size_t)(c > most ? std::min<int64_t>(c, 4 * CHUNK) : c));
             fw += insts[i].M + (int64_t)insts[i].k * ci.W + ci.W;
             kw += c * ci.W;
             sw += ci.buckets - 1;
         }
         facet_words.assign((size_t)fw, 0u);
         splits.assign((size_t)sw, Key{0, 0});
-        if (!xs.reset((size_t)total_n) || !keys.reset((size_t)total_n) || !kv.reset((size_t)kw) ||
-            !bucket_of.reset((size_t)total_n) || (write && !refs.reset((size_t)total_n)))
-            return WPM_ELIMIT;
-        cell0.resize(chunk_tasks.size());
-        int64_t nc = 0;
-        for (size_t t = 0; t < chunk_tasks.size(); ++t) {
-            cell0[t] = nc;
-            nc += cs[chunk_tasks[t].inst].buckets;
-        }
         cells.assign((size_t)nc, Cell{0, 0});
-        starts.assign(bucket_tasks.size(), Cell{0, 0});
+        if (!xs.reset((size_t)total_n) || !kv.reset((size_t)kw) || !bucket_of.reset((size_t)shared) ||
+            (write && !order.reset((size_t)shared)))
+            return WPM_ELIMIT;
         uint32_t *f = facet_words.data(), *v = kv.get();
         Key *sp = splits.data();
         for (int i = 0; i < num; ++i) {
@@ -622,8 +645,32 @@ int collect(const wpm_host_instance *insts, int32_t num, const uint64_t *d_surv,
         }
         return WPM_OK;
     };
+    // the facet list of a bit vector; returns the place after it
+    auto put_list = [](const Collected &c, const uint32_t *K, uint32_t *out) {
+        uint32_t *len = out++;
+        for (int q = 0; q < c.W; ++q)
+            for (uint32_t v = K[q]; v; v &= v - 1) *out++ = c.mask[q * 32 + __builtin_ctz(v)];
+        *len = (uint32_t)(out - len - 1);
+        return out;
+    };
+    auto list_words = [](const Collected &c, const uint32_t *K) {
+        int64_t w = 1;
+        for (int q = 0; q < c.W; ++q) w += __builtin_popcount(K[q]);
+        return w;
+    };
+    // references in canonical order of the bit vectors at `base`
+    auto sort_refs = [](const Collected &c, const uint32_t *base, Ref *r, size_t n) {
+        const int W = c.W;
+        std::sort(r, r + n, [&](const Ref &a, const Ref &b) {
+            if (!(a.key == b.key)) return a.key < b.key;
+            return canon_less(base + (size_t)a.idx * W, base + (size_t)b.idx * W, W);
+        });
+    };
     Team team;
     auto work = [&](int t) {
+        Buffer<uint32_t> own;  // this thread's bit vectors of an instance, and references
+        Buffer<Ref> refs;
+        size_t refs_have = 0;
         team.share(0, ranges, 1, [&](int64_t r) {
             int64_t *h = hist.data() + (size_t)r * num;
             const uint64_t e = std::min<uint64_t>(slots, (uint64_t)(r + 1) * per);
@@ -655,8 +702,12 @@ int collect(const wpm_host_instance *insts, int32_t num, const uint64_t *d_surv,
                 if (inst != ~0ull) xs[(size_t)h[inst]++] = rec[2 * q];
             }
         });
+        refs_have = rows;
+        if (!own.reset(row_words) || !refs.reset(refs_have)) failed = 1;
         team.barrier();
+        if (failed) return;
         // facets, and key ranges by a sample of the instance's results
+        if (t == 0) rec_copy.release();
         team.share(2, num, 4, [&](int64_t i) {
             Collected &c = cs[(size_t)i];
             if (!c.n) return;
@@ -673,30 +724,45 @@ int collect(const wpm_host_instance *insts, int32_t num, const uint64_t *d_surv,
             for (int q = 1; q < c.buckets; ++q) c.split[q - 1] = sample[(int64_t)m * q / c.buckets];
         });
         team.barrier();
-        team.share(3, (int64_t)chunk_tasks.size(), 2, [&](int64_t ct) {
-            const Task tk = chunk_tasks[(size_t)ct];
-            const Collected &c = cs[(size_t)tk.inst];
-            Cell *cell = cells.data() + cell0[(size_t)ct];
+        team.share(3, (int64_t)expand_tasks.size(), 2, [&](int64_t et) {
+            const Task tk = expand_tasks[(size_t)et];
+            Collected &c = cs[(size_t)tk.inst];
+            const int W = c.W;
+            if (tk.sub < 0) {
+                int64_t words = 0;
+                for (int64_t r = 0; r < c.n; ++r) {
+                    uint32_t *K = own.get() + (size_t)r * W;
+                    expand(c, xs[(size_t)(c.first + r)], K);
+                    words += list_words(c, K);
+                    if (write) refs[(size_t)r] = {order_key(K, W), (uint32_t)r};
+                }
+                c.words = words;
+                if (!write) return;
+                sort_refs(c, own.get(), refs.get(), (size_t)c.n);
+                for (int64_t r = 0; r < c.n; ++r)
+                    std::memcpy(c.kv + (size_t)r * W, own.get() + (size_t)refs[(size_t)r].idx * W, sizeof(uint32_t) * W);
+                return;
+            }
+            Cell *cell = cells.data() + cell0[(size_t)et];
             const int64_t r1 = std::min<int64_t>(c.n, (tk.sub + 1) * CHUNK);
             for (int64_t r = tk.sub * CHUNK; r < r1; ++r) {
-                uint32_t *K = c.kv + (size_t)r * c.W;
+                uint32_t *K = c.kv + (size_t)r * W;
                 expand(c, xs[(size_t)(c.first + r)], K);
-                const Key key = order_key(K, c.W);
-                const int b = c.buckets == 1 ? 0 : (int)(std::upper_bound(c.split, c.split + c.buckets - 1, key) - c.split);
-                keys[(size_t)(c.first + r)] = key;
-                bucket_of[(size_t)(c.first + r)] = (uint8_t)b;
+                const Key key = order_key(K, W);
+                const int b = (int)(std::upper_bound(c.split, c.split + c.buckets - 1, key) - c.split);
+                bucket_of[(size_t)(c.shared0 + r)] = (uint8_t)b;
                 ++cell[b].n;
-                int64_t w = 1;
-                for (int q = 0; q < c.W; ++q) w += __builtin_popcount(K[q]);
-                cell[b].words += w;
+                cell[b].words += list_words(c, K);
             }
         });
         team.barrier();
-        // places: per instance, bucket by bucket, chunk by chunk
+        if (t == 0) xs.release();
+        // places: per instance of several ranges, range by range, chunk by chunk
         team.share(4, num, 16, [&](int64_t i) {
             Collected &c = cs[(size_t)i];
+            if (c.buckets == 1) return;
             int64_t n = 0, w = 0;
-            for (int b = 0; c.n && b < c.buckets; ++b) {
+            for (int b = 0; b < c.buckets; ++b) {
                 starts[(size_t)(c.bucket0 + b)] = {n, w};
                 for (int64_t q = 0; q < c.chunks; ++q) {
                     Cell &cell = cells[(size_t)(cell0[(size_t)(c.chunk0 + q)] + b)];
@@ -722,40 +788,43 @@ int collect(const wpm_host_instance *insts, int32_t num, const uint64_t *d_surv,
         }
         team.barrier();
         if (stop) return;
-        team.share(5, (int64_t)chunk_tasks.size(), 4, [&](int64_t ct) {
-            const Task tk = chunk_tasks[(size_t)ct];
+        team.share(5, (int64_t)expand_tasks.size(), 4, [&](int64_t et) {
+            const Task tk = expand_tasks[(size_t)et];
+            if (tk.sub < 0) return;
             const Collected &c = cs[(size_t)tk.inst];
-            Cell *cell = cells.data() + cell0[(size_t)ct];
+            Cell *cell = cells.data() + cell0[(size_t)et];
             const int64_t r1 = std::min<int64_t>(c.n, (tk.sub + 1) * CHUNK);
-            for (int64_t r = tk.sub * CHUNK; r < r1; ++r) {
-                const size_t at = (size_t)(c.first + r);
-                refs[(size_t)(c.first + cell[bucket_of[at]].n++)] = {keys[at], r};
-            }
+            for (int64_t r = tk.sub * CHUNK; r < r1; ++r)
+                order[(size_t)(c.shared0 + cell[bucket_of[(size_t)(c.shared0 + r)]].n++)] = (uint32_t)r;
         });
         team.barrier();
-        // each bucket: canonical order, then the facet lists
-        team.share(6, (int64_t)bucket_tasks.size(), 1, [&](int64_t bt) {
-            const Task tk = bucket_tasks[(size_t)bt];
+        team.share(6, (int64_t)write_tasks.size(), 1, [&](int64_t wt) {
+            const Task tk = write_tasks[(size_t)wt];
             const Collected &c = cs[(size_t)tk.inst];
-            const int W = c.W;
-            Ref *r0 = refs.get() + c.first + starts[(size_t)bt].n;
-            Ref *r1 = refs.get() + c.first + (tk.sub + 1 < c.buckets ? starts[(size_t)bt + 1].n : c.n);
-            std::sort(r0, r1, [&](const Ref &a, const Ref &b) {
-                if (!(a.key == b.key)) return a.key < b.key;
-                return canon_less(c.kv + (size_t)a.idx * W, c.kv + (size_t)b.idx * W, W);
-            });
-            uint32_t *out = h_out + h_offsets[tk.inst] + starts[(size_t)bt].words;
-            for (const Ref *r = r0; r < r1; ++r) {
-                const uint32_t *K = c.kv + (size_t)r->idx * W;
-                uint32_t *len = out++;
-                for (int q = 0; q < W; ++q)
-                    for (uint32_t v = K[q]; v; v &= v - 1) *out++ = c.mask[q * 32 + __builtin_ctz(v)];
-                *len = (uint32_t)(out - len - 1);
+            uint32_t *out = h_out + h_offsets[tk.inst];
+            if (tk.sub < 0) {
+                for (int64_t r = 0; r < c.n; ++r) out = put_list(c, c.kv + (size_t)r * c.W, out);
+                return;
             }
+            const Cell &at = starts[(size_t)(c.bucket0 + tk.sub)];
+            const size_t n = (size_t)((tk.sub + 1 < c.buckets ? starts[(size_t)(c.bucket0 + tk.sub) + 1].n : c.n) - at.n);
+            const uint32_t *idx = order.get() + c.shared0 + at.n;
+            if (n > refs_have) {  // (a range of very many equal keys)
+                refs_have = n;
+                if (!refs.reset(n)) {
+                    refs_have = 0;
+                    failed = 1;
+                    return;
+                }
+            }
+            for (size_t r = 0; r < n; ++r) refs[r] = {order_key(c.kv + (size_t)idx[r] * c.W, c.W), idx[r]};
+            sort_refs(c, c.kv, refs.get(), n);
+            out += at.words;
+            for (size_t r = 0; r < n; ++r) out = put_list(c, c.kv + (size_t)refs[r].idx * c.W, out);
         });
     };
     team.run(want, work);
-    return rc;
+    return failed ? WPM_ELIMIT : rc;
 }
 
 }  // namespace wpm

@@ -442,7 +442,8 @@ typedef struct wpm_sched {
     uint32_t *d_scratch;       /* device: >= 4 words (queue heads), cleared by the call */
     uint64_t *d_item_times;    /* optional device [num_items][2]: start, end (s_memrealtime) */
     const int64_t *d_bin_offsets; /* PACKED mode: device [grid + 1] from wpm_pack_bins */
-    int32_t waves_per_simd;    /* register budget of the kernel: 7 or 8 waves per SIMD (0 = 8) */
+    int32_t waves_per_simd;    /* register budget of the walk: 7 or 8 waves per SIMD (0 = 8; the descent
+                                * has one budget, 7) */
     int32_t scratch_words;     /* WPM_QUEUE_SCRATCH_WORDS: d_scratch holds that many words, and
                                 * the dynamic queue has eight heads instead of one; any other
                                 * value: 4 words */

@@ -1,6 +1,6 @@
-"""Autotuner for the persistent sweep: lane chunk bits, workgroup size and
-the kernel's register budget (7 or 8 waves per SIMD); for a pruned sweep
-also the free coordinates a convenient basis keeps (min_free).
+"""Autotuner for the persistent sweep: lane chunk bits, workgroup size and,
+where tables are walked, the walk's register budget (7 or 8 waves per SIMD); for a
+pruned sweep also the free coordinates a convenient basis keeps (min_free).
 
 It times candidate launch shapes on the batch itself when a sweep of it takes
 well under a second, else on a sample that keeps the batch's mix (every
@@ -58,6 +58,12 @@ def _sample(preps, budget_vectors: float):
         stride += 1
 
 
+def wave_choices(batch: "E.DeviceBatch", waves: Sequence[int]) -> Sequence[int]:
+    """The register budgets worth timing: the descent has one, so the first
+    stands for all of them where every table is descended."""
+    return waves[:1] if batch.c_batch.flags == L.BATCH_TREE else waves
+
+
 def tune(preps: Sequence, cache: Optional[str] = DEFAULT_CACHE, budget_vectors: float = 3e12,
          cbits=CBITS, wgs=WGS, waves=WAVES, repeats: int = 1, force: bool = False, log=None) -> Dict:
     import torch
@@ -77,6 +83,7 @@ def tune(preps: Sequence, cache: Optional[str] = DEFAULT_CACHE, budget_vectors: 
     batch = E.DeviceBatch(sub)
     sw = E.Sweeper(batch, cap=1 << 26)
     vec = batch.visited
+    waves = wave_choices(full, waves)
     results, ref = [], None
     for wg in wgs:
         for cb in cbits:

@@ -62,3 +62,12 @@ def test_walked_short_items(wg):
     assert not walked(n, 64, wg, 6) and not walked(n, 64, 1, 63)
     assert not walked(n - 1, 64, wg - 1, 6) and not walked(0, 64, 1, 7) and not walked(1, 64, 1, 7)
     assert not walked(n, 63, wg - 1, 6)
+
+
+def test_tuner_times_register_budgets_of_walked_tables_alone(preps):
+    from paper_2301_00806_amd import tune as T
+    mixed = E.DeviceBatch(preps, device="cpu")
+    descended = E.DeviceBatch([p for p in preps if E.descended(p)], device="cpu")
+    walked = E.DeviceBatch([p for p in preps if not E.descended(p)], device="cpu")
+    assert T.wave_choices(descended, T.WAVES) == T.WAVES[:1]
+    assert T.wave_choices(walked, T.WAVES) == T.wave_choices(mixed, T.WAVES) == T.WAVES

@@ -145,3 +145,174 @@ def test_short_items_are_walked_in_static_and_packed_launches(E, mode):
         assert [int(c) for c in res.counts] == want and (res.stats[5:8] == 0).all()
     sw.launch_fetch(mode, wg_size=256)
     assert [int(c) for c in sw.result().counts] == want
+
+
+# ----------------------------------------------------------- the walk alone
+
+def walk_batch(E, preps):
+    from paper_2301_00806_amd import _lib as L
+    preps = [walked(p) for p in preps]
+    batch = E.DeviceBatch(preps)
+    assert batch.c_batch.flags == L.BATCH_WALK
+    assert all(b.flags == L.BATCH_WALK for b in batch.class_batches.values())
+    return preps, batch
+
+
+def sweep(E, preps, mode=2, cbits=10, wg=256, waves=0, cap=1 << 22, split=True, **kw):
+    """Sets and result of a sweep of the instances, all of them walked."""
+    preps, batch = walk_batch(E, preps)
+    sw = E.Sweeper(batch, cap=cap)
+    sw.set_items(E.build_queue(batch.k, cbits, wg, blocks=batch.blocks, **kw), split_classes=split)
+    print(f"[gpu] walk of {len(preps)} instances, mode {mode} cbits {cbits} wg {wg} waves {waves}", flush=True)
+    sw.launch(mode, wg_size=wg, waves=waves)
+    res = sw.result()
+    assert (res.stats[5:8] == 0).all()  # (the descent opens sub-cubes)
+    return sw.collect(), res
+
+
+def graphs(E, sizes=(5, 6, 7, 8), **kw):
+    import itertools
+    return [E.prepare(2, v, facets=[(1 << a) | (1 << b) for a, b in itertools.combinations(range(v), 2)],
+                      max_facets=0, **kw) for v in sizes]
+
+
+@pytest.mark.parametrize("waves", [7, 8])
+@pytest.mark.parametrize("cbits,wg", [(13, 128), (10, 512), (7, 64), (12, 256)])
+def test_walk_matches_oracle_under_both_register_budgets(E, waves, cbits, wg):
+    insts = [i for i in W.batch(E.kdim, count=96) if i.meta["k"] <= 20][:16]
+    preps = E.prepare_many(insts)
+    sets, res = sweep(E, preps, cbits=cbits, wg=wg, waves=waves)
+    want = oracle_sets(preps)
+    assert sets == want and list(res.counts) == [len(w) for w in want]
+
+
+@pytest.mark.parametrize("waves", [7, 8])
+def test_walk_across_segments_and_full_lists(E, waves):
+    # chunks of 2^14 steps cross the 4096-step segments; complete graphs fill the
+    # candidate lists, so that overflow steps are rechecked (stats[4])
+    inst = W.single(E.kdim)
+    p = E.prepare(inst.n, inst.m, lam=inst.lam)
+    sets, _ = sweep(E, [p], cbits=14, wg=64, waves=waves)
+    assert sets == oracle_sets([p])
+    preps = graphs(E)
+    sets, res = sweep(E, preps, cbits=12, waves=waves)
+    assert sets == oracle_sets(preps) and int(res.stats[4]) > 0
+
+
+@pytest.mark.parametrize("waves", [7, 8])
+@pytest.mark.parametrize("mode", [0, 1, 2])
+def test_walk_of_a_batch_without_level_sections(E, waves, mode):
+    # six disjoint K_4 have no critical ridge: the packer itself leaves the level
+    # section out
+    from paper_2301_00806_amd import _lib as L
+    import itertools
+    F = [(1 << (4 * g + a)) | (1 << (4 * g + b)) for g in range(6) for a, b in itertools.combinations(range(4), 2)]
+    p = E.prepare(2, 24, facets=F, max_facets=0)
+    assert p.k == 18 and not E.descended(p)
+    batch = E.DeviceBatch([p])
+    assert batch.c_batch.flags == L.BATCH_WALK
+    sw = E.Sweeper(batch, cap=1 << 19)
+    sw.set_items(E.build_queue(batch.k, 8, 128))
+    sw.launch(mode, wg_size=128, waves=waves)
+    res = sw.result()
+    assert res.total == 8 ** 6 - 1 == int(res.counts[0])  # every union of the seven cycles of each
+    counts, words, offs = sw.collect_raw()
+    assert list(offs) == [0, len(words)] and int(counts[0]) == 8 ** 6 - 1
+    one = [[]] + [c for c in oracle_sets(graphs(E, (4,)))[0]]
+    assert len(one) == 8 and len(words) == 8 ** 6 - 1 + 6 * 8 ** 5 * sum(map(len, one))
+
+
+def test_walk_of_cosets_and_properties(E):
+    from test_conditions import _conditions_for, oracle_filtered
+    insts = [W.fano()] + [i for i in W.batch(E.kdim, count=64) if i.meta["k"] <= 18][:11]
+    preps, wants = [], []
+    for j, inst in enumerate(insts):
+        F = E.candidates(inst.n, inst.m, inst.lam)
+        mf = E.default_max_facets(inst.n, inst.m)
+        I, J, props = _conditions_for(inst.n, F, mf, j)
+        kw = [dict(forced_in=I, forced_out=J), dict(properties=props),
+              dict(forced_in=I, forced_out=J, properties=props)][j % 3]
+        preps.append(E.prepare(inst.n, inst.m, lam=inst.lam, **kw))
+        wants.append(oracle_filtered(inst.n, F, mf, kw.get("forced_in") or (), kw.get("forced_out") or (),
+                                     kw.get("properties") or ()))
+    assert any(p.offset is not None for p in preps)
+    for cbits, wg, mode, waves in ((7, 64, 2, 7), (9, 256, 1, 8), (12, 256, 0, 7)):
+        sets, res = sweep(E, preps, mode=mode, cbits=cbits, wg=wg, waves=waves)
+        assert sets == wants and list(res.counts) == [len(w) for w in wants]
+
+
+def test_walk_of_mixed_strides_and_deferred_ridges(E):
+    insts = [i for i in W.batch(E.kdim, count=48) if 14 <= i.meta["k"] <= 20][:8]
+    preps = [E.prepare(i.n, i.m, lam=i.lam, max_groups=1 + j % 2) for j, i in enumerate(insts)]
+    preps += graphs(E, (7, 8)) + graphs(E, (7, 8), max_groups=1)
+    assert {p.info.slots for p in preps} == {4, 8} and sum(p.info.n_deferred for p in preps) > 0
+    want = oracle_sets(preps)
+    for mode, cbits, waves in ((2, 9, 7), (0, 7, 8), (1, 10, 8)):
+        sets, res = sweep(E, preps, mode=mode, cbits=cbits, waves=waves, split=False)
+        assert sets == want and list(res.counts) == [len(w) for w in want]
+
+
+@pytest.mark.parametrize("policy", ["plain", "static", "dynamic", "packed"])
+def test_walk_schedules(E, policy):
+    from paper_2301_00806_amd import scheduler as S
+    insts = [i for i in W.batch(E.kdim, count=96) if i.meta["k"] <= 20][:24]
+    preps, batch = walk_batch(E, E.prepare_many(insts))
+    want = oracle_sets(preps)
+    sw = E.Sweeper(batch, cap=1 << 22)
+    plan = S.make_plan(batch, policy, cbits=9, wg=256, plain_min_items=3)
+    sw.set_items(plan.items, segments=plan.segments)
+    sw.launch(plan.mode, wg_size=256)
+    sw.result()
+    assert sw.collect() == want
+    rec = np.asarray(sw.launch_fetch(plan.mode, wg_size=256, parts=3))
+    assert (rec[:, 1] != -1).sum() == sum(len(w) for w in want)
+
+
+def test_walk_of_a_pruned_batch(E):
+    insts = [i for i in W.batch(E.kdim, count=96) if i.meta["k"] <= 20][:24]
+    preps = E.prepare_many(insts, prune=True, min_free=10)
+    assert sum(p.visited for p in preps) < sum(p.vectors for p in preps)
+    sets, _ = sweep(E, preps, cbits=9, order=1, cost=np.arange(1, len(preps) + 1, dtype=np.float32))
+    assert sets == oracle_sets(preps)
+
+
+@pytest.mark.parametrize("mode", [1, 2])
+def test_walk_skips_and_counts_malformed_items(E, mode):
+    from paper_2301_00806_amd import _lib as L
+    insts = [i for i in W.batch(E.kdim, count=32) if i.meta["k"] <= 16][:3]
+    preps = E.prepare_many(insts)
+    want = oracle_sets(preps)
+    alone, batch = walk_batch(E, preps[:2])
+    both = E.DeviceBatch(alone + preps[2:])
+    good = E.build_queue(batch.k, 7, 64)
+    bad = np.zeros(5, dtype=E.ITEM_DTYPE)
+    bad[0] = (0, 5, 64, 0)                                   # cbits < 7
+    bad[1] = (0, 7, 64, 480)                                 # 480 + 64 > 512
+    bad[2] = (1, 7, 64, (1 << (max(preps[1].k, 7) - 7)))     # beyond 2^k
+    bad[3] = (1 << 20, 7, 64, 0)                             # unknown instance
+    bad[4] = (2, 7, 64, 0)                                   # a table of the other kind
+    batch = both
+    batch.c_batch.flags = L.BATCH_WALK
+    sw = E.Sweeper(batch, cap=1 << 20)
+    sw.set_items(np.concatenate([good, bad]), split_classes=False)
+    print("[gpu] malformed items under the walk", flush=True)
+    sw.launch(mode, wg_size=64, grid=2)
+    torch.cuda.synchronize()
+    assert int(sw.total.cpu()[2]) == 5
+    assert [int(c) for c in sw.counts.cpu()] == [len(want[0]), len(want[1]), 0]
+    with pytest.raises(L.WpmError):
+        sw.collect()
+
+
+def test_walk_counts_are_exact_after_record_overflow(E):
+    from paper_2301_00806_amd import _lib as L
+    preps, batch = walk_batch(E, graphs(E, (7, 8), max_groups=1))
+    want = [O.count_wpm(p.n, [int(f) for f in p.facets], p.max_facets) for p in preps]
+    sw = E.Sweeper(batch, cap=64)
+    sw.set_items(E.build_queue(batch.k, 8, 64))
+    sw.launch(2, wg_size=64)
+    res = sw.result()
+    assert res.slots > 64 and [int(c) for c in res.counts] == want
+    with pytest.raises(L.WpmError) as ei:
+        sw.collect()
+    assert ei.value.status == L.WPM_ECAP

@@ -417,8 +417,8 @@ typedef struct wpm_batch {
 } wpm_batch;
 
 /* Two kernels share the sweep: tables with a level section (header word 11,
- * bit 1, set by wpm_pack_instance when the sub-cube tests reject enough) are
- * descended as a tree, the others walked vector by vector.  A batch that says
+ * bit 1; wpm_pack_instance gives one to every table) are descended as a tree,
+ * the others walked vector by vector.  A batch that says
  * that all of its tables are of one kind is spared the other's launch; an
  * item whose table is of the other kind is then malformed (d_total[2]). */
 #define WPM_BATCH_TREE 1 /* every table swept has a level section */

@@ -46,9 +46,6 @@ constexpr int LV_SIX = 4;       // 64-vector sub-cubes, two groups
 constexpr int LV_TWELVE = 12;   // 4096-vector sub-cubes
 constexpr int LV_EIGHTEEN = 16; // 2^18-vector sub-cubes
 constexpr int WPM_LEVEL_WORDS = 20;
-// Instances that get a level section.
-constexpr int WPM_TREE_SMALL_K = 16;
-constexpr double WPM_TREE_MAX_PASS = 0.75;
 
 struct Incidence {
     int n = 0, M = 0, N = 0;

@@ -335,11 +335,9 @@ std::vector<LevelRidge> pick_level(const std::vector<LevelRidge> &all, int most,
     return out;
 }
 
-// The ridges of the tree descent, and the share of 64-vector sub-cubes that
-// the tests of 12 and 6 free coordinates leave.
+// The ridges of the tree descent.
 struct LevelPlan {
     std::vector<LevelRidge> leaf, six, twelve, eighteen;
-    double pass6 = 1.0;
 };
 
 }  // namespace
@@ -514,51 +512,49 @@ int pack_instance(int n, int m, const uint32_t *facets, int32_t M, const uint32_
     // Tree descent: ridges for sub-cubes of 2^18, 2^12 and 2^6 vectors, ranked on the
     // first samples, then the leaf ridges, ranked on all 64 vectors of the
     // sub-cubes that pass (sample words: one sub-cube each, bit r = its vector
-    // with low coordinates r).
+    // with low coordinates r).  Every table gets a level section: the descent is
+    // the faster one also where its tests reject nothing (dynamic sweeps of 16
+    // graphs, walked / descended: eight disjoint K_4, k = 24, every vector a
+    // complex, 25.3 / 6.6 ms; K_6 and five K_4, k = 25, 87% of the sub-cubes
+    // left, 10.4 / 2.7; five disjoint K_4, k = 15, 0.27 / 0.26).
     LevelPlan lv;
-    bool tree = k <= WPM_TREE_SMALL_K;
     {
         const int tw = std::min(TW, 256);
         auto col = [&](int32_t j) -> const uint64_t * { return cols.data() + (size_t)fcol[j] * TW; };
         std::vector<uint64_t> up(tw, ~0ull);
         if (tw == TW) up[tw - 1] = tail_mask;
-        const int64_t up0 = count_bits(up.data(), up.size());
         lv.eighteen = pick_level(level_ridges(inc, crit, frow, 18), 32, tw, col, up);
         lv.twelve = pick_level(level_ridges(inc, crit, frow, 12), 32, tw, col, up);
         lv.six = pick_level(level_ridges(inc, crit, frow, 6), 64, tw, col, up);
-        lv.pass6 = (double)count_bits(up.data(), up.size()) / (double)up0;
-        tree = tree || lv.pass6 <= WPM_TREE_MAX_PASS;
-        if (tree) {
-            std::vector<int32_t> cube;  // samples of sub-cubes that pass (any, when none does)
-            for (int w = 0; w < tw; ++w)
-                for (uint64_t b = up[w]; b && cube.size() < 128; b &= b - 1)
-                    cube.push_back(w * 64 + __builtin_ctzll(b));
-            if (cube.empty())
-                for (int q = 0; q < std::min(T, 64); ++q) cube.push_back(q);
-            const int cw = (int)cube.size();
-            static const uint64_t bitpat[6] = {0xAAAAAAAAAAAAAAAAull, 0xCCCCCCCCCCCCCCCCull,
-                                               0xF0F0F0F0F0F0F0F0ull, 0xFF00FF00FF00FF00ull,
-                                               0xFFFF0000FFFF0000ull, 0xFFFFFFFF00000000ull};
-            std::vector<uint64_t> xlow(cw, 0);  // low coordinates of the samples themselves
-            for (int t = 0; t < std::min(k, 6); ++t)
-                for (int q = 0; q < cw; ++q)
-                    xlow[q] |= ((X[(size_t)t * TW + cube[q] / 64] >> (cube[q] % 64)) & 1ull) << t;
-            std::vector<uint64_t> cc((size_t)std::max(nf, 1) * cw);
-            for (int j = 0; j < M; ++j) {
-                if (fcol[j] < 0) continue;
-                const uint64_t fl = frow[j] & 63u, *cj = col(j);
-                uint64_t pat = 0;
-                for (uint64_t b = fl; b; b &= b - 1) pat ^= bitpat[__builtin_ctzll(b)];
-                for (int q = 0; q < cw; ++q) {
-                    const uint64_t own = (cj[cube[q] / 64] >> (cube[q] % 64)) & 1ull;
-                    const uint64_t base = own ^ (uint64_t)(__builtin_popcountll(fl & xlow[q]) & 1);
-                    cc[(size_t)fcol[j] * cw + q] = pat ^ (0ull - base);
-                }
+        std::vector<int32_t> cube;  // samples of sub-cubes that pass (any, when none does)
+        for (int w = 0; w < tw; ++w)
+            for (uint64_t b = up[w]; b && cube.size() < 128; b &= b - 1)
+                cube.push_back(w * 64 + __builtin_ctzll(b));
+        if (cube.empty())
+            for (int q = 0; q < std::min(T, 64); ++q) cube.push_back(q);
+        const int cw = (int)cube.size();
+        static const uint64_t bitpat[6] = {0xAAAAAAAAAAAAAAAAull, 0xCCCCCCCCCCCCCCCCull,
+                                           0xF0F0F0F0F0F0F0F0ull, 0xFF00FF00FF00FF00ull,
+                                           0xFFFF0000FFFF0000ull, 0xFFFFFFFF00000000ull};
+        std::vector<uint64_t> xlow(cw, 0);  // low coordinates of the samples themselves
+        for (int t = 0; t < std::min(k, 6); ++t)
+            for (int q = 0; q < cw; ++q)
+                xlow[q] |= ((X[(size_t)t * TW + cube[q] / 64] >> (cube[q] % 64)) & 1ull) << t;
+        std::vector<uint64_t> cc((size_t)std::max(nf, 1) * cw);
+        for (int j = 0; j < M; ++j) {
+            if (fcol[j] < 0) continue;
+            const uint64_t fl = frow[j] & 63u, *cj = col(j);
+            uint64_t pat = 0;
+            for (uint64_t b = fl; b; b &= b - 1) pat ^= bitpat[__builtin_ctzll(b)];
+            for (int q = 0; q < cw; ++q) {
+                const uint64_t own = (cj[cube[q] / 64] >> (cube[q] % 64)) & 1ull;
+                const uint64_t base = own ^ (uint64_t)(__builtin_popcountll(fl & xlow[q]) & 1);
+                cc[(size_t)fcol[j] * cw + q] = pat ^ (0ull - base);
             }
-            std::vector<uint64_t> all(cw, ~0ull);
-            lv.leaf = pick_level(level_ridges(inc, crit, frow, 0), 32, cw,
-                                 [&](int32_t j) -> const uint64_t * { return cc.data() + (size_t)fcol[j] * cw; }, all);
         }
+        std::vector<uint64_t> all(cw, ~0ull);
+        lv.leaf = pick_level(level_ridges(inc, crit, frow, 0), 32, cw,
+                             [&](int32_t j) -> const uint64_t * { return cc.data() + (size_t)fcol[j] * cw; }, all);
     }
     std::vector<uint64_t>().swap(cols);
     std::vector<uint64_t>().swap(X);
@@ -638,7 +634,7 @@ int pack_instance(int n, int m, const uint32_t *facets, int32_t M, const uint32_
     const int RS = ((4 + (G - 1) * QS + W) + 3) & ~3;
     const int nrows = kp + (offset ? 1 : 0);  // the offset row follows the basis rows
     const int64_t level_at = (int64_t)WPM_HDR_WORDS + (int64_t)nrows * RS;
-    const int64_t props_at = level_at + (tree ? (int64_t)nrows * WPM_LEVEL_WORDS : 0);
+    const int64_t props_at = level_at + (int64_t)nrows * WPM_LEVEL_WORDS;
     const int64_t defer_at = props_at + (nprops ? 2 * (int64_t)nprops + (int64_t)nclasses * (1 + W) : 0);
     const int64_t words = defer_at + defer_words;
 
@@ -674,7 +670,7 @@ int pack_instance(int n, int m, const uint32_t *facets, int32_t M, const uint32_
     h[HDR_MAXF] = (uint32_t)max_facets;
     h[HDR_NCRIT] = (uint32_t)n_crit;
     h[HDR_NFILT] = (uint32_t)filt.size();
-    h[HDR_FLAGS] = (offset ? HDR_FLAG_OFFSET : 0u) | (tree ? HDR_FLAG_TREE : 0u);
+    h[HDR_FLAGS] = (offset ? HDR_FLAG_OFFSET : 0u) | HDR_FLAG_TREE;
     h[HDR_PROPS] = nprops ? (uint32_t)props_at : 0u;
     h[HDR_NPROPS] = (uint32_t)nprops;
     h[HDR_DEFER] = deferred.empty() ? 0u : (uint32_t)defer_at;
@@ -720,30 +716,28 @@ int pack_instance(int n, int m, const uint32_t *facets, int32_t M, const uint32_
     if (offset)
         for (int w = 0; w < W; ++w) rows[(size_t)kp * RS + koff + w] = offset[w];
     // level section: the sub-cube tests' slot words of every row
-    if (tree) {
-        uint32_t *lrows = table + level_at;
-        auto place_level = [&](const std::vector<LevelRidge> &lr, size_t from, int word_base) {
-            for (size_t i = from; i < std::min(lr.size(), from + 32); ++i) {
-                const uint32_t bit = 1u << (i - from);
-                for (int q = 0; q < lr[i].np; ++q) {
-                    const int32_t f = lr[i].par[q];
-                    for (uint64_t b = frow[f]; b; b &= b - 1)
-                        lrows[(size_t)__builtin_ctzll(b) * WPM_LEVEL_WORDS + word_base + q] |= bit;
-                    if (offj[f]) lrows[(size_t)kp * WPM_LEVEL_WORDS + word_base + q] |= bit;
-                }
+    uint32_t *lrows = table + level_at;
+    auto place_level = [&](const std::vector<LevelRidge> &lr, size_t from, int word_base) {
+        for (size_t i = from; i < std::min(lr.size(), from + 32); ++i) {
+            const uint32_t bit = 1u << (i - from);
+            for (int q = 0; q < lr[i].np; ++q) {
+                const int32_t f = lr[i].par[q];
+                for (uint64_t b = frow[f]; b; b &= b - 1)
+                    lrows[(size_t)__builtin_ctzll(b) * WPM_LEVEL_WORDS + word_base + q] |= bit;
+                if (offj[f]) lrows[(size_t)kp * WPM_LEVEL_WORDS + word_base + q] |= bit;
             }
-            for (int t = 0; t < nrows; ++t) {
-                uint32_t *r = lrows + (size_t)t * WPM_LEVEL_WORDS + word_base;
-                r[1] ^= r[0];
-                r[3] ^= r[2];
-            }
-        };
-        place_level(lv.leaf, 0, LV_LEAF);
-        place_level(lv.six, 0, LV_SIX);
-        place_level(lv.six, 32, LV_SIX + 4);
-        place_level(lv.twelve, 0, LV_TWELVE);
-        place_level(lv.eighteen, 0, LV_EIGHTEEN);
-    }
+        }
+        for (int t = 0; t < nrows; ++t) {
+            uint32_t *r = lrows + (size_t)t * WPM_LEVEL_WORDS + word_base;
+            r[1] ^= r[0];
+            r[3] ^= r[2];
+        }
+    };
+    place_level(lv.leaf, 0, LV_LEAF);
+    place_level(lv.six, 0, LV_SIX);
+    place_level(lv.six, 32, LV_SIX + 4);
+    place_level(lv.twelve, 0, LV_TWELVE);
+    place_level(lv.eighteen, 0, LV_EIGHTEEN);
     // property section: c0, class count, then (weight, W mask words) per class
     uint32_t *pr = table + props_at;
     for (int q = 0, cls = 0; q < nprops; ++q) {

@@ -1,9 +1,9 @@
 """Tables without a level section on the GPU: the walk of every vector, alone
 and in one launch with descended tables, against the oracle.
 
-The packer gives nearly every table a level section, so these tests take the
-bit that announces it out of the header (the rest of the table does not
-depend on it) and check which kernel a batch gets."""
+The packer gives every table a level section, so these tests take the bit that
+announces it out of the header (the rest of the table does not depend on it)
+and check which kernel a batch gets."""
 import copy
 import ctypes
 
@@ -131,7 +131,7 @@ def test_short_items_are_walked_in_static_and_packed_launches(E, mode):
     from paper_2301_00806_amd import scheduler as S
     insts = [i for i in W.batch(E.kdim, count=160) if 16 < i.meta["k"] <= 24]
     preps = E.prepare_many(insts, prune=True, min_free=7)
-    preps = [p for p in preps if E.descended(p)]
+    assert all(E.descended(p) for p in preps)
     batch = E.DeviceBatch(preps)
     sw = E.Sweeper(batch, cap=1 << 22)
     plan = S.make_plan(batch, {1: "static", 3: "packed"}[mode], cbits=7, wg=256)
@@ -201,16 +201,16 @@ def test_walk_across_segments_and_full_lists(E, waves):
 
 @pytest.mark.parametrize("waves", [7, 8])
 @pytest.mark.parametrize("mode", [0, 1, 2])
-def test_walk_of_a_batch_without_level_sections(E, waves, mode):
-    # six disjoint K_4 have no critical ridge: the packer itself leaves the level
-    # section out
+@pytest.mark.parametrize("kind", ["walked", "descended"])
+def test_sweep_without_critical_ridges(E, waves, mode, kind):
+    # six disjoint K_4 have no critical ridge: every vector is a complex
     from paper_2301_00806_amd import _lib as L
     import itertools
     F = [(1 << (4 * g + a)) | (1 << (4 * g + b)) for g in range(6) for a, b in itertools.combinations(range(4), 2)]
     p = E.prepare(2, 24, facets=F, max_facets=0)
-    assert p.k == 18 and not E.descended(p)
-    batch = E.DeviceBatch([p])
-    assert batch.c_batch.flags == L.BATCH_WALK
+    assert p.k == 18 and p.info.n_crit == 0
+    batch = E.DeviceBatch([walked(p) if kind == "walked" else p])
+    assert batch.c_batch.flags == (L.BATCH_WALK if kind == "walked" else L.BATCH_TREE)
     sw = E.Sweeper(batch, cap=1 << 19)
     sw.set_items(E.build_queue(batch.k, 8, 128))
     sw.launch(mode, wg_size=128, waves=waves)

@@ -1,5 +1,7 @@
 """Launch classes of a batch: each holds tables of one kind, so that no launch
 looks at the items of the other kernel (host logic, no GPU)."""
+import itertools
+
 import numpy as np
 import pytest
 
@@ -10,11 +12,24 @@ from paper_2301_00806_amd import engine as E
 
 @pytest.fixture(scope="module")
 def preps():
-    # convenient bases with few free coordinates: some tables have no level section
     insts = [i for i in W.batch(E.kdim, count=96) if i.meta["k"] <= 22][:48]
     out = E.prepare_many(insts, prune=True, min_free=7)
+    for p in out[::3]:
+        p.table[11] &= ~np.uint32(2)  # without the bit that announces the level section
     assert {E.descended(p) for p in out} == {True, False}
     return out
+
+
+def test_every_packed_table_has_a_level_section():
+    # also where its tests reject nothing: disjoint K_4 have no critical ridge
+    for groups in (1, 5, 6, 8):
+        F = [(1 << (4 * g + a)) | (1 << (4 * g + b)) for g in range(groups)
+             for a, b in itertools.combinations(range(4), 2)]
+        p = E.prepare(2, 4 * groups, facets=F, max_facets=0)
+        assert p.k == 3 * groups and p.info.n_crit == 0 and E.descended(p)
+    insts = [i for i in W.batch(E.kdim, count=128) if i.meta["k"] <= 20]
+    for mf in (7, 10):
+        assert all(E.descended(p) for p in E.prepare_many(insts, prune=True, min_free=mf))
 
 
 def test_classes_hold_one_kind(preps):

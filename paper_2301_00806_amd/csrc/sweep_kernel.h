@@ -1,6 +1,8 @@
 // The Gray-code walk of the F2 kernel on gfx950 (device code): it visits
-// every vector.  Instances whose tables have a level section are swept by
-// tree descent instead (tree_kernel.h), which shares the final checks here.
+// every vector.  Tables with a level section are swept by tree descent instead
+// (tree_kernel.h), which shares the final checks here; the walk is left to
+// tables without one and to launches that ask for it, static and packed ones of
+// many short items.
 //
 // Every lane owns a chunk of 2^c consecutive Gray indices i of one instance
 // and visits x = i ^ (i >> 1), so consecutive vectors differ in the single

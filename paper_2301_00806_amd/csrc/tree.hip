@@ -1,5 +1,5 @@
-// Instantiation of the tree descent: 8 waves per SIMD, since its waves are
-// chains of dependent scalar and vector operations.
+// Instantiation of the tree descent: 7 waves per SIMD, as many as its LDS leaves
+// room for, since its waves are chains of dependent scalar and vector operations.
 #include "launch.h"
 #include "tree_kernel.h"
 

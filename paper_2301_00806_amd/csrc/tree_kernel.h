@@ -1,5 +1,5 @@
 // The tree descent of the F2 kernel on gfx950 (device code): the sweep of
-// every instance whose table has a level section.
+// every table that has a level section (the packer gives one to all).
 //
 // A range of Gray indices is descended as a tree of aligned sub-cubes with
 // fan-out 64: blocks of 2^24 vectors, groups of 2^18, nodes of 2^12, children
@@ -32,13 +32,14 @@
 // chains; the descent makes no memory accesses.  Survivors cluster (in the
 // vectors with few high coordinates, and in small kernels), so a group with
 // many surviving nodes is shared by the waves of the workgroup, and items are
-// split and spread over the workgroups by the host.
+// spread over the workgroups, in parts where there are few.
 //
-// Measured against the walk of every vector (ms a sweep, same outputs): 1024
-// maps of n = 5..8, k <= 34, 7.4e10 vectors 8.1 -> 1.1; 512 of n = 4..7 1.72 ->
-// 0.44; three facet sets of 7-subsets of [11], k = 32..36, 10.5 -> 0.62; a slice
-// of 1.5e10 pruned vectors of an n = 9 orbit 1.77 -> 0.11.  16384 maps of n = 5..8,
-// k <= 36, 1.04e12 vectors: 114 -> 7.4.
+// Measured against the walk of every vector (ms a sweep, the same inputs and
+// outputs, two seeds): 1024 maps of n = 5..8, 6e10 vectors 9.9, 7.5 -> 1.12, 0.90;
+// 512 of n = 4..7 1.87, 1.45 -> 0.40, 0.34; 512 over convenient bases 1.88, 1.61 ->
+// 0.50, 0.45; three facet sets of 7-subsets of [11], k = 32..36, 11.3, 5.2 -> 0.40,
+// 0.70; a slice of 1.5e10 pruned vectors of an n = 9 orbit 1.70 -> 0.11.  16384
+// maps of n = 5..8, k <= 36, 1.04e12 vectors: 113 -> 7.3.
 #pragma once
 
 #include "sweep_kernel.h"
@@ -79,8 +80,8 @@ __host__ __device__ constexpr int tree_stride(int RS) { return RS | 4; }
 //   [kp-17][20]           level rows of coordinates 17 and up
 //   [56][S]               Gray-bit tables of the staged instance (bits 0-20)
 //   [nw][S]               per-wave window rows
-// With the static part under 20 KB for 256 threads, RS = 44, kp = 36: eight
-// workgroups in a CU.
+// For 256 threads, RS = 44, kp = 36 that is 19.3 KB, with the static part 20.2 KB:
+// seven workgroups, as many as the registers allow, in the 160 KB of a CU.
 __host__ __device__ constexpr size_t tree_lds_bytes(int max_kp, int max_row_words, int wg_size) {
     const size_t nw = (size_t)(wg_size / 64), kp = (size_t)max_kp;
     const size_t up = kp > GROUP_BITS - 1 ? kp - (GROUP_BITS - 1) : 0;
@@ -110,7 +111,7 @@ void tree_kernel(const uint32_t *__restrict__ tables, const int64_t *__restrict_
     extern __shared__ __attribute__((aligned(16))) uint32_t lds_dyn[];
     // The launch arguments, read from LDS where they are used.
     __shared__ KArgs s_a;
-    // Counters that every workgroup adds to serialise at 7-11 ns an access on
+    // Counters that every workgroup adds to serialise at about 12 ns an access on
     // this chip, whatever the access does: 8192 waves adding six statistics
     // words each took longer than the sweep of a thousand instances.  So a
     // workgroup takes several items from the queue at a time, reserves record

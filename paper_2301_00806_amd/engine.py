@@ -300,9 +300,9 @@ ITEM_DTYPE = np.dtype([("instance", "<u4"), ("cbits", "<u2"), ("lanes", "<u2"), 
 
 # Row widths that bound a launch's LDS layout.  One kernel sweeps every
 # instance; a launch sizes each workgroup's LDS for its widest table, so
-# instances are launched in classes of similar width: 8 workgroups of 256
-# threads fit a compute unit up to 44 words per row (with kp <= 36), 6 up to
-# 64.
+# instances are launched in classes of similar width: 7 workgroups of 256
+# threads fit a compute unit up to 44 words per row (with kp <= 36; 8 of the
+# walk), 6 up to 64.
 LDS_CLASSES = (44, 64, 96, L.MAX_ROW_WORDS)
 
 
